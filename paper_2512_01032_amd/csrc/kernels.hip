@@ -51,6 +51,39 @@ hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Sum of a diagnostic sweep's per-tile partials: one workgroup per quantity,
+// each thread over a fixed set of tiles, then a fixed tree, so the result does
+// not depend on scheduling.  Bound by the latency of its loads (40960 tiles of
+// the 256 x 256 x 512 duct are 3.3 MB), hence 1024 threads with four loads in
+// flight each.  A kernel of its own, because letting the sweep's last tile do
+// it takes an agent-scope release per tile, which writes back an XCD's L2: a
+// diagnostic sweep of that duct took 5168 us against 876 us of a plain one.
+constexpr int REDUCE_THREADS = 1024;
+__global__ void __launch_bounds__(REDUCE_THREADS) diag_reduce_kernel(Desc* __restrict__ D) {
+    __shared__ double s_red[REDUCE_THREADS / 64];
+    const int j = blockIdx.x, tid = threadIdx.x;
+    const int nt = D->ntiles;
+    const double* __restrict__ p = D->partials + (int64_t)j * nt;
+    const bool mx = j == P_UMAX;
+    auto join = [&](double a, double b) { return mx ? fmax(a, b) : a + b; };
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int t = tid; t < nt; t += 4 * REDUCE_THREADS) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (t + k * REDUCE_THREADS < nt) v[k] = join(v[k], p[t + k * REDUCE_THREADS]);
+    }
+    double r = join(join(v[0], v[1]), join(v[2], v[3]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) r = join(r, __shfl_xor(r, o, 64));
+    if ((tid & 63) == 0) s_red[tid >> 6] = r;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < REDUCE_THREADS / 64; ++w) r = join(r, s_red[w]);
+    D->diag[j] = r;
+    if (j == 0) D->diag_step = D->step;
+    if ((j == P_NAN && r > 0.0) || (mx && D->u_max > 0.0 && r > D->u_max)) D->unstable = 1;
+}
+
 hipError_t launch_advance(Desc* d, int nlat, hipStream_t s) {
     if (nlat <= 0) return hipSuccess;
     advance_kernel<<<dim3((nlat + NTHREADS - 1) / NTHREADS), dim3(NTHREADS), 0, s>>>(d, nlat);
@@ -81,13 +114,16 @@ hipError_t launch_wall(int storage, int mode, const Desc* d, const WallRef* wall
 
 hipError_t launch_sweep(int storage, int qp, int mode, int tx, int parity, Desc* d, const Tile* tiles,
                         int ntiles, int diag, ReadOut ro, InitIn in, hipStream_t s) {
+    hipError_t e = hipErrorInvalidValue;
     switch (storage) {
-        case ST_FP64: return launch_sweep_fp64(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
+        case ST_FP64: e = launch_sweep_fp64(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s); break;
         case ST_FP32:
-        case ST_FP32_SHIFT: return launch_sweep_fp32(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
-        case ST_FP16_G: return launch_sweep_fp16g(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
+        case ST_FP32_SHIFT: e = launch_sweep_fp32(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s); break;
+        case ST_FP16_G: e = launch_sweep_fp16g(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s); break;
     }
-    return hipErrorInvalidValue;
+    if (e != hipSuccess || ntiles <= 0 || !diag) return e;
+    diag_reduce_kernel<<<dim3(NPART), dim3(REDUCE_THREADS), 0, s>>>(d);
+    return hipGetLastError();
 }
 
 hipError_t launch_phi(int storage, int qp, int parity, const Desc* d, const Tile* tiles, int ntiles,

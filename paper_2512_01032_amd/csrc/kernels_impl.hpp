@@ -20,8 +20,8 @@
 //                  free-slip band at solid links (Sec. III.A)
 //                - pressure-ghost equilibria written by the ghost's owner
 //              FP64 wavefront/LDS reductions of mass, momentum, |u|max and
-//              phase pressures on diagnostic steps; the last tile of a lattice
-//              reduces the tile partials in a fixed order.
+//              phase pressures on diagnostic steps, one set of partials per
+//              tile, which a kernel of its own sums in a fixed order.
 //
 // AA pattern (the populations are updated in place).  At an even step node x
 // reads f_i from slot (x, i) and writes f*_i to (x, opp(i)); at an odd step it
@@ -734,7 +734,6 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
     __shared__ T s_phi[4][LN];
     __shared__ uint8_t s_flag[4][LN];
     __shared__ double s_red[NPART][NTHREADS / 64];
-    __shared__ int s_last;
     // sub-voxel instance: f_i^in of each solid link i, kept by the thread
     // that read it from the stream step to its write-back
     __shared__ T s_fin[SV ? QG - 1 : 1][NTHREADS];
@@ -1250,68 +1249,23 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
         lds_barrier();
     }
 
-    // Only a diagnostic pass needs tiles to meet: a cross-tile handshake costs
-    // an agent-scope release and acquire per tile (L2 write-back and
-    // invalidate on a chip whose XCDs have separate L2s).  The step counter
-    // advances in its own kernel.
     if (MODE == MODE_INIT || !(DIAG && diag)) return;
 
-    // ---- per-tile FP64 partials (wavefront shuffle -> LDS), then the last
-    //      tile of the lattice reduces them in a fixed order
-    {
-        const int lane = tid & 63, wv = tid >> 6;
+    // ---- per-tile FP64 partials (wavefront shuffle -> LDS), one row per
+    //      quantity; diag_reduce_kernel sums them after the sweep
+    const int lane = tid & 63, wv = tid >> 6;
 #pragma unroll
-        for (int j = 0; j < NPART; ++j) {
-            const double v = (j == P_UMAX) ? wave_max(acc[j]) : wave_sum(acc[j]);
-            if (lane == 0) s_red[j][wv] = v;
-        }
-        __syncthreads();
-        if (tid < NPART) {
-            double v = s_red[tid][0];
-            for (int w = 1; w < NTHREADS / 64; ++w)
-                v = (tid == P_UMAX) ? fmax(v, s_red[tid][w]) : v + s_red[tid][w];
-            D->partials[(int64_t)tl.tile_in_lat * NPART + tid] = v;
-        }
+    for (int j = 0; j < NPART; ++j) {
+        const double v = (j == P_UMAX) ? wave_max(acc[j]) : wave_sum(acc[j]);
+        if (lane == 0) s_red[j][wv] = v;
     }
     __syncthreads();
-    if (tid == 0) {
-        __threadfence();
-        const unsigned old = __hip_atomic_fetch_add(D->counter, 1u, __ATOMIC_ACQ_REL,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        s_last = (old == (unsigned)uni(D->ntiles) - 1u);
+    if (tid < NPART) {
+        double v = s_red[tid][0];
+        for (int w = 1; w < NTHREADS / 64; ++w)
+            v = (tid == P_UMAX) ? fmax(v, s_red[tid][w]) : v + s_red[tid][w];
+        D->partials[(int64_t)tid * uni(D->ntiles) + tl.tile_in_lat] = v;
     }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    {
-        // fixed-order reduction: thread t sums tiles t, t+256, ... then a tree
-        const int nt = uni(D->ntiles);
-        for (int j = 0; j < NPART; ++j) {
-            double v = 0.0;
-            for (int t = tid; t < nt; t += NTHREADS) {
-                const double p = __hip_atomic_load(&D->partials[(int64_t)t * NPART + j],
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                v = (j == P_UMAX) ? fmax(v, p) : v + p;
-            }
-            v = (j == P_UMAX) ? wave_max(v) : wave_sum(v);
-            if ((tid & 63) == 0) s_red[j][tid >> 6] = v;
-        }
-        __syncthreads();
-        if (tid < NPART) {
-            double v = s_red[tid][0];
-            for (int w = 1; w < NTHREADS / 64; ++w)
-                v = (tid == P_UMAX) ? fmax(v, s_red[tid][w]) : v + s_red[tid][w];
-            D->diag[tid] = v;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            D->diag_step = step;
-            const bool nan = D->diag[P_NAN] > 0.0;
-            const bool fast = D->u_max > 0.0 && D->diag[P_UMAX] > D->u_max;
-            if (nan || fast) D->unstable = 1;
-        }
-    }
-    if (tid == 0) __hip_atomic_store(D->counter, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 

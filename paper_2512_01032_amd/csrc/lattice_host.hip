@@ -207,7 +207,7 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
     face_planes(p, L);
     size_t o = 0;
     L->off_desc = o; o = align256(o + sizeof(Desc));
-    L->off_counter = o; o = align256(o + sizeof(unsigned int));
+    o = align256(o + sizeof(unsigned int));
     {
         const PopLayout pl = pop_layout(phase_q(p), sh, sg);
         L->pop_bytes = (size_t)pop_group_bytes(p);
@@ -443,7 +443,6 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
     d->wall = p->subvoxel ? (void*)(base + L.off_wall) : nullptr;
     for (int f = 0; f < 6; ++f) d->gface_base[f] = L.gface_base[f];
     d->gface_count = L.gface_count;
-    d->counter = (unsigned int*)(base + L.off_counter);
     d->step = step;
     d->t0 = 0;
     d->stop_step = INT64_MAX;
@@ -540,7 +539,6 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     // zero populations and phi (solid slots stay zero), upload geometry
     HIPCHK(hipMemsetAsync(base + L.off_pop0, 0, L.pop_bytes, s));
     if (L.off_pop1 != L.off_pop0) HIPCHK(hipMemsetAsync(base + L.off_pop1, 0, L.pop_bytes, s));
-    HIPCHK(hipMemsetAsync(base + L.off_counter, 0, sizeof(unsigned int), s));
     HIPCHK(hipMemsetAsync(base + L.off_partials, 0, L.tiles.size() * NPART * sizeof(double), s));
     HIPCHK(hipMemcpyAsync(base + L.off_flag, L.flag.data(), N, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(base + L.off_link, L.link.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));

@@ -96,8 +96,7 @@ struct alignas(256) Desc {
     void* phi;
     const uint8_t* flag;
     const uint32_t* link;
-    double* partials;              // [ntiles][NPART]
-    unsigned int* counter;         // tiles finished in the current sweep
+    double* partials;              // [NPART][ntiles]
     void* gbuf;                    // [3][face entries] u of each ghost's owner (compute type)
     int64_t gface_base[6];         // first entry of each face plane in gbuf
     int64_t gface_count;           // entries per velocity component
@@ -202,6 +201,8 @@ struct InitIn {                // device inputs of MODE_INIT
 // force: run the phi pass even for lattices past their stop step (read-back).
 hipError_t launch_phi(int storage, int qp, int parity, const Desc* d, const Tile* tiles, int ntiles,
                       hipStream_t s, int force = 0);
+// diag: the sweep of a diagnostic step or a read pass, of lattice d alone; a
+// second kernel reduces the tiles' partials into d->diag and the stability flag.
 hipError_t launch_sweep(int storage, int qp, int mode, int tx, int parity, Desc* d, const Tile* tiles,
                         int ntiles, int diag, ReadOut ro, InitIn in, hipStream_t s);
 hipError_t launch_restore(int storage, int qp, int parity, const Desc* d, const Tile* tiles, int ntiles,
