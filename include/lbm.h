@@ -207,12 +207,14 @@ int lbm_create(const lbm_params *p, const lbm_geometry *geo, const lbm_init *ini
 /* Queue nsteps time steps on the handle's stream and return.  Each step is
  * the phi pass, the wall pass (wetting values and stencil sums of the
  * near-wall nodes, Sec. II.B), the fused stream-collide sweep (Sec. II.A,
- * Eqs. 1-16), the pressure-face ghosts (Sec. III.A) and the step counter.
- * The steps are replayed from HIP graphs captured at the first call (one
- * step per AA parity and diagnostic kind, and 16-step runs without a
+ * Eqs. 1-16), the pressure-face ghosts (Sec. III.A) and the step counter; for
+ * lattices in the fused layout (D3Q7 phase lattice, whole-voxel walls, at most
+ * 512 MB of populations) all of them are one kernel.  The steps are replayed
+ * from HIP graphs captured when first needed (one step per AA parity and
+ * diagnostic kind, unless a step is one kernel, and 16-step runs without a
  * diagnostic step); while timing is on (lbm_set_timing) every kernel is
- * launched on its own between events instead.  Both give bitwise the same
- * state.  Returns LBM_E_UNSTABLE if a diagnostic taken before this call
+ * launched on its own between events instead.  All of these give bitwise the
+ * same state.  Returns LBM_E_UNSTABLE if a diagnostic taken before this call
  * flagged NaN or |u| > u_max (sticky). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 
@@ -260,9 +262,9 @@ int lbm_reduce(lbm_handle *h, lbm_diag *d);
 /* Optional per-kernel timing with HIP events on the handle's stream: while on,
  * lbm_step launches each kernel on its own and records events around them;
  * lbm_get_timing returns the accumulated milliseconds of the phi pass with
- * the wall pass, and of the sweep kernel alone (the ghost and step-counter
- * kernels that follow it are not bracketed), and the number of steps timed,
- * and resets them. */
+ * the wall pass (none in the fused layout), and of the sweep kernel alone (the
+ * ghost and step-counter kernels that follow it are not bracketed), and the
+ * number of steps timed, and resets them. */
 int lbm_set_timing(lbm_handle *h, int32_t on);
 int lbm_get_timing(lbm_handle *h, double *phi_ms, double *sweep_ms, int64_t *steps);
 
@@ -283,9 +285,9 @@ int lbm_get_info(const lbm_handle *h, lbm_info *info);
 /* ------------------------------------------------------------------ serving
  * Continuous batching of many independent lattices on one GPU: requests are
  * admitted when their footprint fits the HBM budget and a slot is free, every
- * admitted lattice advances one step per tick in one batched phi pass and one
- * batched sweep over a device table of (lattice, tile) work items, and
- * finished lattices are read back and their memory reused. */
+ * admitted lattice advances one step per tick in one batched sweep over a
+ * device table of (lattice, tile) work items, with a batched phi pass before it
+ * for lattices in the separate-pass layout, and finished lattices are read back and their memory reused. */
 typedef struct lbm_server_cfg {
     size_t hbm_budget;       /* bytes of device memory for lattices (0: 80% of free) */
     int32_t max_slots;       /* lattices resident at once (<= 256) */

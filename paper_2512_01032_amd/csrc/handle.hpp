@@ -38,11 +38,11 @@ struct lbm_handle {
     size_t ev_used = 0;
     double phi_ms = 0.0, sweep_ms = 0.0;
     int64_t steps_timed = 0;
-    // replayed step sequences (captured on a private stream at the first
-    // untimed lbm_step): one step by [parity][diagnostic], and GRAPH_CHUNK
-    // steps without a diagnostic step by starting parity
+    // replayed step sequences (captured on a private stream when an untimed
+    // lbm_step first needs them): GRAPH_CHUNK steps without a diagnostic step
+    // by starting parity, and, for separate passes, one step by
+    // [parity][diagnostic]
     hipStream_t cap_stream = nullptr;
-    bool graphs_ready = false;
     hipGraphExec_t one[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     hipGraphExec_t chunk[2] = {nullptr, nullptr};
 };

@@ -80,7 +80,6 @@ __global__ void __launch_bounds__(REDUCE_THREADS) diag_reduce_kernel(Desc* __res
     if (tid != 0) return;
     for (int w = 1; w < REDUCE_THREADS / 64; ++w) r = join(r, s_red[w]);
     D->diag[j] = r;
-    if (j == 0) D->diag_step = D->step;
     if ((j == P_NAN && r > 0.0) || (mx && D->u_max > 0.0 && r > D->u_max)) D->unstable = 1;
 }
 

@@ -1,4 +1,5 @@
-// kernels_impl.hpp -- CDNA4 (gfx950) kernels of the phase-field LB step.
+// kernels_impl.hpp -- CDNA4 (gfx950) kernels of the phase-field LB step, as
+// separate passes (kernels_fused.hpp: the step as one kernel).
 //
 // Per time step, over a tile table (one lattice, or many lattices of a
 // serving batch) and a list of near-wall fluid nodes:
@@ -128,7 +129,7 @@ template <typename SH, typename SG, int QP> struct Lay {
 template <typename S_, int Q_, int U0, typename LAY> struct PopArray {
     typedef S_ S;
     static constexpr int Q = Q_;
-    static constexpr bool IS_G = U0 > 0;
+    static constexpr bool IS_G = U0 > 0;   // (false for g alone, Lay<SG, SG, 0>, whose SZH is g's)
     __amdgpu_buffer_rsrc_t r0, r1;
     __device__ __amdgpu_buffer_rsrc_t rs(int q) const { return U0 + q < LAY::K ? r0 : r1; }
     __device__ static constexpr uint32_t so(int q) {
@@ -581,6 +582,88 @@ __device__ inline void h_eq_pair(int i, const NodeState<T>& s, T href, T& hp, T&
     hm = w * (e - o);
 }
 
+// Unit normal into the fluid from the solid links of a voxel wall.
+template <typename T>
+__device__ inline void wall_normal(uint32_t solid, T* nw) {
+    nw[0] = nw[1] = nw[2] = T(0);
+#pragma unroll
+    for (int i = 1; i < 19; ++i) {
+        if (!((solid >> i) & 1u)) continue;
+        nw[0] -= T(wg(i) * CX[i]); nw[1] -= T(wg(i) * CY[i]); nw[2] -= T(wg(i) * CZ[i]);
+    }
+    const T nn = dev_sqrt(nw[0] * nw[0] + nw[1] * nw[1] + nw[2] * nw[2]);
+    const T inn = nn > T(0) ? dev_div(T(1), nn) : T(0);
+    nw[0] *= inn; nw[1] *= inn; nw[2] *= inn;
+}
+
+// Gradient and Laplacian sums of one near-wall node (out[0..3]: x, y, z,
+// Laplacian) from its phi pc, the phi nv[i] of its fluid and ghost
+// neighbours (0 at solid ones), the solid-link mask, the materials mw of the
+// solid links (4 bits each), the wall normal nw and the contact angles' cos
+// and sin.  PP: the lattice's derived constants (indexable).  hist: the node's
+// history entries (stride nwl; NULL without hysteresis).
+template <typename T, int MODE, typename PP>
+__device__ inline void wall_sums(uint32_t solid, T pc, const T* nv, const uint32_t* mw, const T* nw,
+                                 const T (*s_cs)[16], const PP& pp, int hmode, bool record, T* hist,
+                                 int64_t nwl, T* out) {
+    const T iTg = T(3);
+    T gx = T(0), gy = T(0), gz = T(0), lap = T(0);
+    auto pair_sum = [&](int i, T vp, T vm) {
+        const T dv = vp - vm;
+        if (CX[i]) gx += T(wg(i) * CX[i]) * dv;
+        if (CY[i]) gy += T(wg(i) * CY[i]) * dv;
+        if (CZ[i]) gz += T(wg(i) * CZ[i]) * dv;
+        lap += T(wg(i)) * ((vp - pc) + (vm - pc));
+    };
+#pragma unroll
+    for (int i = 1; i < 19; i += 2)
+        pair_sum(i, ((solid >> i) & 1u) ? pc : nv[i], ((solid >> (i + 1)) & 1u) ? pc : nv[i + 1]);
+    const T g0[3] = {gx * iTg, gy * iTg, gz * iTg};
+    const T ng = nw[0] * g0[0] + nw[1] * g0[1] + nw[2] * g0[2];
+    T gt[3] = {g0[0] - nw[0] * ng, g0[1] - nw[1] * ng, g0[2] - nw[2] * ng};
+    const T tnn = dev_sqrt(gt[0] * gt[0] + gt[1] * gt[1] + gt[2] * gt[2]);
+    const T itn = dev_div(T(1), tnn + pp[PI_EPS]);
+    gt[0] *= itn; gt[1] *= itn; gt[2] *= itn;
+    T a = T(2) * pc - T(1);
+    a = a > T(1) - pp[PI_CLAMP_A] ? T(1) - pp[PI_CLAMP_A] : a;
+    a = a < -T(1) + pp[PI_CLAMP_A] ? -T(1) + pp[PI_CLAMP_A] : a;
+    const T k2W = pp[PI_K2W];
+    // contact-angle hysteresis (Sec. III.A): the wall value of link i is
+    // blended with one kept from the previous step (history [18][n_wall]):
+    // the blended value that step used (mode 1) or its unblended value
+    // (mode 2); initialisation and a reset pass record the current values
+    auto phis = [&](int i) -> T {
+        const int mat = (mw[(i - 1) / 6] >> (4 * ((i - 1) % 6))) & 15u;
+        const T ct = s_cs[0][mat], sn = s_cs[1][mat];
+        const T d = -ct * cdot(i, nw[0], nw[1], nw[2]) + sn * cdot(i, gt[0], gt[1], gt[2]);
+        // tanh(artanh(a) + 2d/W) by the addition theorem: phi_s,i is exactly
+        // phi(x) where d_i = 0 (a link along the normal of a 90-degree wall),
+        // so the Laplacian there is exactly zero as in the FP64 model and the
+        // sign term of the mobility correction does not flip on rounding noise
+        const T t = dev_tanh(k2W * d);
+        T ps = T(0.5) * (T(1) + dev_div(a + t, T(1) + a * t));
+        if (hmode) {
+            T* hp = hist + (int64_t)(i - 1) * nwl;
+            if (record) {
+                *hp = ps;
+            } else {
+                const T fresh = ps;
+                ps = pp[PI_HBETA] * *hp + pp[PI_HBETA1] * fresh;
+                if (MODE == MODE_STEP) *hp = hmode == 2 ? fresh : ps;
+            }
+        }
+        return ps;
+    };
+    gx = gy = gz = lap = T(0);
+#pragma unroll
+    for (int i = 1; i < 19; i += 2) {
+        const T vp = ((solid >> i) & 1u) ? phis(i) : nv[i];
+        const T vm = ((solid >> (i + 1)) & 1u) ? phis(i + 1) : nv[i + 1];
+        pair_sum(i, vp, vm);
+    }
+    out[0] = gx; out[1] = gy; out[2] = gz; out[3] = lap;
+}
+
 // ---------------------------------------------------------------- wall pass
 // Every near-wall fluid node, after the phi pass (Sec. II.B, Eqs. 17-19): the
 // wall normal into the fluid from the solid links (sub-voxel walls: from the
@@ -625,7 +708,6 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
     const T* __restrict__ phig = unip((const T*)D->phi);
     const uint32_t solid = wr.solid;
     const T* pp = unip(param_block<T>(D));
-    const T iTg = T(3);
     const int xs[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
     const int ys[3] = {y == 0 ? ny - 1 : y - 1, y, y == ny - 1 ? 0 : y + 1};
     const int zs[3] = {z == 0 ? nz - 1 : z - 1, z, z == nz - 1 ? 0 : z + 1};
@@ -639,14 +721,6 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
     const uint32_t* __restrict__ wm = unip(D->wmat);
     const uint32_t mw[3] = {wm[sl], wm[nwl + sl], wm[2 * nwl + sl]};
     const T pc = phig[n];
-    T gx = T(0), gy = T(0), gz = T(0), lap = T(0);
-    auto pair_sum = [&](int i, T vp, T vm) {
-        const T dv = vp - vm;
-        if (CX[i]) gx += T(wg(i) * CX[i]) * dv;
-        if (CY[i]) gy += T(wg(i) * CY[i]) * dv;
-        if (CZ[i]) gz += T(wg(i) * CZ[i]) * dv;
-        lap += T(wg(i)) * ((vp - pc) + (vm - pc));
-    };
     T nw[3] = {T(0), T(0), T(0)};
     if (uni(D->subvoxel)) {
         const T* __restrict__ wtab = unip((const T*)D->wall);
@@ -654,69 +728,18 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
         nw[1] = wtab[QG * nwl + sl];
         nw[2] = wtab[(QG + 1) * nwl + sl];
     } else {
-#pragma unroll
-        for (int i = 1; i < 19; ++i) {
-            if (!((solid >> i) & 1u)) continue;
-            nw[0] -= T(wg(i) * CX[i]); nw[1] -= T(wg(i) * CY[i]); nw[2] -= T(wg(i) * CZ[i]);
-        }
-        const T nn = dev_sqrt(nw[0] * nw[0] + nw[1] * nw[1] + nw[2] * nw[2]);
-        const T inn = nn > T(0) ? dev_div(T(1), nn) : T(0);
-        nw[0] *= inn; nw[1] *= inn; nw[2] *= inn;
+        wall_normal(solid, nw);
     }
-#pragma unroll
-    for (int i = 1; i < 19; i += 2)
-        pair_sum(i, ((solid >> i) & 1u) ? pc : nv[i], ((solid >> (i + 1)) & 1u) ? pc : nv[i + 1]);
-    const T g0[3] = {gx * iTg, gy * iTg, gz * iTg};
-    const T ng = nw[0] * g0[0] + nw[1] * g0[1] + nw[2] * g0[2];
-    T gt[3] = {g0[0] - nw[0] * ng, g0[1] - nw[1] * ng, g0[2] - nw[2] * ng};
-    const T tnn = dev_sqrt(gt[0] * gt[0] + gt[1] * gt[1] + gt[2] * gt[2]);
-    const T itn = dev_div(T(1), tnn + pp[PI_EPS]);
-    gt[0] *= itn; gt[1] *= itn; gt[2] *= itn;
-    T a = T(2) * pc - T(1);
-    a = a > T(1) - pp[PI_CLAMP_A] ? T(1) - pp[PI_CLAMP_A] : a;
-    a = a < -T(1) + pp[PI_CLAMP_A] ? -T(1) + pp[PI_CLAMP_A] : a;
-    const T k2W = pp[PI_K2W];
-    // contact-angle hysteresis (Sec. III.A): the wall value of link i is
-    // blended with one kept from the previous step (history [18][n_wall]):
-    // the blended value that step used (mode 1) or its unblended value
-    // (mode 2); initialisation and a reset pass record the current values
     const int hmode = uni(D->hysteresis);
-    T* __restrict__ hist = hmode ? unip((T*)D->hyst) : nullptr;
+    T* __restrict__ hist = hmode ? unip((T*)D->hyst) + sl : nullptr;
     const bool record = MODE == MODE_INIT || (MODE == MODE_READ && uni(D->hyst_reset) != 0);
-    auto phis = [&](int i) -> T {
-        const int mat = (mw[(i - 1) / 6] >> (4 * ((i - 1) % 6))) & 15u;
-        const T ct = s_cs[0][mat], sn = s_cs[1][mat];
-        const T d = -ct * cdot(i, nw[0], nw[1], nw[2]) + sn * cdot(i, gt[0], gt[1], gt[2]);
-        // tanh(artanh(a) + 2d/W) by the addition theorem: phi_s,i is exactly
-        // phi(x) where d_i = 0 (a link along the normal of a 90-degree wall),
-        // so the Laplacian there is exactly zero as in the FP64 model and the
-        // sign term of the mobility correction does not flip on rounding noise
-        const T t = dev_tanh(k2W * d);
-        T ps = T(0.5) * (T(1) + dev_div(a + t, T(1) + a * t));
-        if (hmode) {
-            T* hp = hist + (int64_t)(i - 1) * nwl + sl;
-            if (record) {
-                *hp = ps;
-            } else {
-                const T fresh = ps;
-                ps = pp[PI_HBETA] * *hp + pp[PI_HBETA1] * fresh;
-                if (MODE == MODE_STEP) *hp = hmode == 2 ? fresh : ps;
-            }
-        }
-        return ps;
-    };
-    gx = gy = gz = lap = T(0);
-#pragma unroll
-    for (int i = 1; i < 19; i += 2) {
-        const T vp = ((solid >> i) & 1u) ? phis(i) : nv[i];
-        const T vm = ((solid >> (i + 1)) & 1u) ? phis(i + 1) : nv[i + 1];
-        pair_sum(i, vp, vm);
-    }
+    T sums[4];
+    wall_sums<T, MODE>(solid, pc, nv, mw, nw, s_cs, pp, hmode, record, hist, nwl, sums);
     T* __restrict__ out = unip((T*)D->wgl);
-    out[sl] = gx;
-    out[nwl + sl] = gy;
-    out[2 * nwl + sl] = gz;
-    out[3 * nwl + sl] = lap;
+    out[sl] = sums[0];
+    out[nwl + sl] = sums[1];
+    out[2 * nwl + sl] = sums[2];
+    out[3 * nwl + sl] = sums[3];
     out[4 * nwl + sl] = nw[0];
     out[5 * nwl + sl] = nw[1];
     out[6 * nwl + sl] = nw[2];
@@ -1380,6 +1403,12 @@ ghost_kernel(const Desc* __restrict__ descs, const GhostRef* __restrict__ ghosts
 }
 
 
+}  // namespace pflbm
+
+#include "kernels_fused.hpp"
+
+namespace pflbm {
+
 // -------------------------------------------------------------- launchers
 template <typename T>
 hipError_t launch_wall_compute(int mode, const Desc* d, const WallRef* walls, int nwalls, hipStream_t s) {
@@ -1448,6 +1477,7 @@ template <typename T, typename SH, typename SG>
 hipError_t launch_sweep_storage(int qp, int mode, int tx, int parity, Desc* d, const Tile* tiles,
                                 int ntiles, int diag, ReadOut ro, InitIn in, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
+    if (is_fused(qp)) return launch_step<T, SH, SG>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
     if (qp == 19) return launch_sweep_q<T, SH, SG, 19>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
     return launch_sweep_q<T, SH, SG, QH>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
 }
@@ -1472,12 +1502,14 @@ hipError_t launch_restore_storage(int qp, int parity, const Desc* d, const Tile*
                                   const double* pops, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
     dim3 grid(ntiles), block(NTHREADS);
-    const int key = (qp == 19 ? 2 : 0) + (parity & 1);
+    const int key = (is_fused(qp) ? 4 : (qp == 19 ? 2 : 0)) + (parity & 1);
     switch (key) {
         case 0: restore_kernel<T, SH, SG, 0, QH><<<grid, block, 0, s>>>(d, tiles, pops); break;
         case 1: restore_kernel<T, SH, SG, 1, QH><<<grid, block, 0, s>>>(d, tiles, pops); break;
         case 2: restore_kernel<T, SH, SG, 0, 19><<<grid, block, 0, s>>>(d, tiles, pops); break;
-        default: restore_kernel<T, SH, SG, 1, 19><<<grid, block, 0, s>>>(d, tiles, pops); break;
+        case 3: restore_kernel<T, SH, SG, 1, 19><<<grid, block, 0, s>>>(d, tiles, pops); break;
+        case 4: fused_restore_kernel<T, SH, SG, 0><<<grid, block, 0, s>>>(d, tiles, pops); break;
+        default: fused_restore_kernel<T, SH, SG, 1><<<grid, block, 0, s>>>(d, tiles, pops); break;
     }
     return hipGetLastError();
 }

@@ -145,9 +145,15 @@ int choose_tx(int nx) {
     return best;
 }
 
-int choose_tz(const lbm_params* p, int tx) {
+// Tile depth asked for in the environment (0: none).
+static int tile_z_env() {
     const char* env = getenv("LBM_TILE_Z");
-    if (env && atoi(env) > 0) return std::min(atoi(env), p->nz);
+    return env ? std::max(atoi(env), 0) : 0;
+}
+
+int choose_tz(const lbm_params* p, int tx, bool fused) {
+    if (fused) return 1;   // one node per thread
+    if (tile_z_env() > 0) return std::min(tile_z_env(), p->nz);
     const int ty = NTHREADS / tx;
     const int64_t cols = (int64_t)((p->nx + tx - 1) / tx) * ((p->ny + ty - 1) / ty);
     // Short z-chunks: a tile's set-up (three staged phi planes) is cheap, and
@@ -199,6 +205,38 @@ static void face_planes(const lbm_params* p, LatticeLayout* L) {
     L->gface_count = b;
 }
 
+// Bytes of one h buffer and of one g group of the fused layout.
+static int64_t h_buffer_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    const int tx = choose_tx(p->nx);
+    return (int64_t)((p->nx + tx - 1) / tx * tx) * p->ny * p->nz * QH * sh;
+}
+static int64_t g_group_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    return (int64_t)pad_row(p->nx) * p->ny * p->nz * pop_layout(0, sg, sg).pb;
+}
+// Whether a lattice takes the fused layout (one kernel per step): D3Q7 phase
+// lattice, whole-voxel walls, and populations (two h buffers and g) of at most
+// 512 MB, so that those of its non-solid tiles live in the 256 MB Infinity Cache
+// from step to step or nearly so.  us per step of an n x n x 2n constricted duct
+// (30 % solid), separate passes / fused:
+//   FP32    n = 64: 40.2 / 22.7    96: 82.0 / 53.8   112: 134.6 / 134.4   160: 301 / 322   256: 1060 / 1127
+//   FP64    n = 64: 61.9 / 49.2    80: 90.3 / 67.1    96: 142.9 / 140.2   128: 304 / 314
+//   FP16 g  n = 64: 38.6 / 20.2    96: 75.4 / 47.8   128: 125.0 / 125.1   160: 251 / 259   256:  781 /  825
+// (n = 112, 96 and 128 hold 371, 467 and 394 MB).  Beyond, HBM bounds both: an
+// update in place runs at 5.9 TB/s and a copy at 4.8, and the fused step moves h
+// from one buffer to the other.
+constexpr int64_t FUSED_MAX_BYTES = (int64_t)512 << 20;
+static bool fits_fused(const lbm_params* p) {
+    if (phase_q(p) != QH || p->subvoxel) return false;
+    if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    return 2 * h_buffer_bytes(p) + pop_layout(0, sg, sg).G * g_group_bytes(p) <= FUSED_MAX_BYTES;
+}
+
 static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
                            LatticeLayout* L) {
     int sh, sg, sphi;
@@ -207,6 +245,24 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
     face_planes(p, L);
     size_t o = 0;
     L->off_desc = o; o = align256(o + sizeof(Desc));
+    if (L->fused) {
+        const PopLayout pl = pop_layout(0, sg, sg);
+        L->pop_bytes = (size_t)g_group_bytes(p);
+        L->off_pop0 = o; o = align256(o + L->pop_bytes);
+        L->off_pop1 = L->off_pop0;
+        if (pl.G == 2) { L->off_pop1 = o; o = align256(o + L->pop_bytes); }
+        L->h_bytes = (size_t)h_buffer_bytes(p);
+        L->off_h0 = o; o = align256(o + L->h_bytes);
+        L->off_h1 = o; o = align256(o + L->h_bytes);
+        L->off_flag = o; o = align256(o + (size_t)N);
+        L->off_link = o; o = align256(o + (size_t)N * 4);
+        L->off_tiles = o; o = align256(o + (size_t)ntiles * sizeof(Tile));
+        L->off_partials = o; o = align256(o + (size_t)ntiles * NPART * sizeof(double));
+        L->off_wslot = o; if (p->hysteresis) o = align256(o + (size_t)N * 4);
+        L->off_hyst = o; if (p->hysteresis) o = align256(o + (size_t)(QG - 1) * L->n_wall * sphi);
+        L->total = o;
+        return;
+    }
     o = align256(o + sizeof(unsigned int));
     {
         const PopLayout pl = pop_layout(phase_q(p), sh, sg);
@@ -238,7 +294,7 @@ size_t footprint_bytes(const lbm_params* p) {
     if (validate_params(p, nullptr) != LBM_OK) return 0;
     LatticeLayout L;
     L.N = (int64_t)p->nx * p->ny * p->nz;
-    const int tx = choose_tx(p->nx), ty = NTHREADS / tx, tz = choose_tz(p, tx);
+    const int tx = choose_tx(p->nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, false);
     const int64_t ntiles = (int64_t)((p->nx + tx - 1) / tx) * ((p->ny + ty - 1) / ty) *
                            ((p->nz + tz - 1) / tz);
     face_planes(p, &L);
@@ -247,7 +303,7 @@ size_t footprint_bytes(const lbm_params* p) {
     return L.total;
 }
 
-int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeLayout* L) {
+int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fused, LatticeLayout* L) {
     int rc = validate_params(p, geo);
     if (rc != LBM_OK) return rc;
     const int nx = p->nx, ny = p->ny, nz = p->nz;
@@ -287,6 +343,8 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeL
             }
     L->n_fluid = nf; L->n_ghost = ng; L->n_solid = ns;
     if (nf == 0) { set_error("the lattice has no fluid node"); return LBM_E_INVAL; }
+    bool one_kernel = fused && fits_fused(p);
+    L->ghosts.clear();
     // ghost owners
     for (int z = 0; z < nz; ++z)
         for (int y = 0; y < ny; ++y)
@@ -303,7 +361,16 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeL
                 L->ghosts.push_back(GhostRef{lat, (int32_t)n});
                 L->flag[o] |= F_OWNER;
                 L->link[o] |= 1u << (LINK_OWNER_SHIFT + face);
+                // a fluid node behind the ghost (across a periodic wrap that
+                // has a pressure face on one side only) would read entries
+                // that nothing feeds: such a lattice keeps the separate passes
+                for (int i = 1; i < 19; ++i) {
+                    const int cn = (ax == 0 ? HCX[i] : (ax == 1 ? HCY[i] : HCZ[i])) * sg;
+                    if (cn < 0 && flag_kind(L->flag[idx(x + HCX[i], y + HCY[i], z + HCZ[i])]) == KIND_FLUID)
+                        one_kernel = false;
+                }
             }
+    L->fused = one_kernel;
     // solid links of fluid nodes
     for (int z = 0; z < nz; ++z) {
         const int64_t Z[3] = {(int64_t)((z + nz - 1) % nz) * nx * ny, (int64_t)z * nx * ny,
@@ -323,18 +390,21 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeL
             }
         }
     }
-    // slots of the near-wall fluid nodes, in node order (coalesced along x)
+    // slots of the near-wall fluid nodes, in node order (coalesced along x);
+    // the fused layout needs them for the hysteresis table only
     L->n_wall = 0;
     std::vector<double>().swap(L->wall);
-    L->wslot.assign(N, -1);
+    const bool slots = !L->fused || p->hysteresis;
+    L->wslot.assign(slots ? N : 0, -1);
     L->walls.clear();
     for (int64_t n = 0; n < N; ++n)
         if ((L->link[n] & SOLID_MASK) && flag_kind(L->flag[n]) == KIND_FLUID) {
-            L->walls.push_back(WallRef{0, (int32_t)n, (int32_t)L->n_wall, L->link[n] & SOLID_MASK});
-            L->wslot[n] = (int32_t)L->n_wall++;
+            if (!L->fused) L->walls.push_back(WallRef{0, (int32_t)n, (int32_t)L->n_wall, L->link[n] & SOLID_MASK});
+            if (slots) L->wslot[n] = (int32_t)L->n_wall;
+            ++L->n_wall;
         }
     // materials of the solid links, packed per slot
-    L->wmat.assign((size_t)3 * L->n_wall, 0u);
+    L->wmat.assign(L->fused ? 0 : (size_t)3 * L->n_wall, 0u);
     for (const WallRef& w : L->walls) {
         const int64_t n = w.node;
         const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((int64_t)nx * ny));
@@ -391,7 +461,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeL
                 }
     }
     // tile table: keep tiles holding at least one non-solid node
-    const int tx = choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx);
+    const int tx = choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
     L->tiles.clear();
     for (int z0 = 0; z0 < nz; z0 += tz)
@@ -426,18 +496,26 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
     d->Np = (int64_t)d->nxp * p->ny * p->nz;
     d->pops[0] = base + L.off_pop0;
     d->pops[1] = base + L.off_pop1;
-    d->phi = base + L.off_phi;
     d->flag = (const uint8_t*)(base + L.off_flag);
     d->link = (const uint32_t*)(base + L.off_link);
     d->partials = (double*)(base + L.off_partials);
-    d->gbuf = base + L.off_gbuf;
+    d->step2[step & 1] = step;
+    if (L.fused) {
+        d->nxh = (p->nx + L.tx - 1) / L.tx * L.tx;
+        d->hb[0] = base + L.off_h0;
+        d->hb[1] = base + L.off_h1;
+        d->hbytes = h_buffer_bytes(p);
+    } else {
+        d->phi = base + L.off_phi;
+        d->gbuf = base + L.off_gbuf;
+        d->wgl = base + L.off_wgl;
+        d->wmat = (const uint32_t*)(base + L.off_wmat);
+    }
     d->q_phase = phase_q(p);
     d->hysteresis = p->hysteresis;
     d->hyst_reset = 0;
     d->n_wall = L.n_wall;
     d->wslot = (const int32_t*)(base + L.off_wslot);
-    d->wgl = base + L.off_wgl;
-    d->wmat = (const uint32_t*)(base + L.off_wmat);
     d->hyst = p->hysteresis ? (void*)(base + L.off_hyst) : nullptr;
     d->subvoxel = p->subvoxel ? 1 : 0;
     d->wall = p->subvoxel ? (void*)(base + L.off_wall) : nullptr;
@@ -542,8 +620,13 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     HIPCHK(hipMemsetAsync(base + L.off_partials, 0, L.tiles.size() * NPART * sizeof(double), s));
     HIPCHK(hipMemcpyAsync(base + L.off_flag, L.flag.data(), N, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(base + L.off_link, L.link.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(base + L.off_wslot, L.wslot.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
-    if (L.n_wall) {
+    if (L.fused) {
+        HIPCHK(hipMemsetAsync(base + L.off_h0, 0, L.h_bytes, s));
+        HIPCHK(hipMemsetAsync(base + L.off_h1, 0, L.h_bytes, s));
+    }
+    if (!L.wslot.empty())
+        HIPCHK(hipMemcpyAsync(base + L.off_wslot, L.wslot.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
+    if (!L.walls.empty()) {
         HIPCHK(hipMemcpyAsync(base + L.off_wrefs, L.walls.data(), L.walls.size() * sizeof(WallRef),
                               hipMemcpyHostToDevice, s));
         HIPCHK(hipMemcpyAsync(base + L.off_wmat, L.wmat.data(), L.wmat.size() * 4, hipMemcpyHostToDevice, s));
@@ -564,17 +647,17 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     }
     HIPCHK(hipMemcpyAsync(base + L.off_tiles, L.tiles.data(), L.tiles.size() * sizeof(Tile),
                           hipMemcpyHostToDevice, s));
-    if (!L.ghosts.empty())
+    if (!L.fused && !L.ghosts.empty())
         HIPCHK(hipMemcpyAsync(base + L.off_ghosts, L.ghosts.data(), L.ghosts.size() * sizeof(GhostRef),
                               hipMemcpyHostToDevice, s));
-    if (L.gface_count)
+    if (!L.fused && L.gface_count)
         HIPCHK(hipMemsetAsync(base + L.off_gbuf, 0, (size_t)3 * L.gface_count * sphi, s));
     const int64_t step0 = (init && init->kind == LBM_INIT_POPULATIONS) ? init->step : 0;
     fill_desc(p, geo, L, base, step0, hdesc);
     HIPCHK(hipMemcpyAsync(base + L.off_desc, hdesc, sizeof(Desc), hipMemcpyHostToDevice, s));
     Desc* ddesc = (Desc*)(base + L.off_desc);
     const Tile* dtiles = (const Tile*)(base + L.off_tiles);
-    const int nt = (int)L.tiles.size();
+    const int nt = (int)L.tiles.size(), lq = launch_q(*hdesc);
     if (!init) { set_error("init is NULL"); return LBM_E_INVAL; }
     if (init->kind == LBM_INIT_POPULATIONS) {
         if (!init->pops) { set_error("POPULATIONS init needs pops"); return LBM_E_INVAL; }
@@ -582,7 +665,7 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
         HIPCHK(hipMalloc(&dpops, (size_t)(phase_q(p) + QG) * N * sizeof(double)));
         hipError_t e = hipMemcpyAsync(dpops, init->pops, (size_t)(phase_q(p) + QG) * N * sizeof(double),
                                       hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = launch_restore(p->storage, phase_q(p), (int)(step0 & 1), ddesc, dtiles, nt, dpops, s);
+        if (e == hipSuccess) e = launch_restore(p->storage, lq, (int)(step0 & 1), ddesc, dtiles, nt, dpops, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         hipFree(dpops);
         if (e != hipSuccess) { set_error("restore: %s", hipGetErrorString(e)); return LBM_E_DEVICE; }
@@ -593,7 +676,7 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
             HIPCHK(hipMemcpyAsync(&ddesc->hyst_reset, &on, sizeof(on), hipMemcpyHostToDevice, s));
             HIPCHK(hipStreamSynchronize(s));
             int rc = read_lattice(p->storage, *hdesc, (int)(step0 & 1), ddesc, dtiles, nt,
-                                  (const WallRef*)(base + L.off_wrefs), (int)L.n_wall, 0, nullptr,
+                                  (const WallRef*)(base + L.off_wrefs), (int)L.walls.size(), 0, nullptr,
                                   nullptr, nullptr, nullptr, s);
             HIPCHK(hipMemcpyAsync(&ddesc->hyst_reset, &off, sizeof(off), hipMemcpyHostToDevice, s));
             HIPCHK(hipStreamSynchronize(s));
@@ -620,7 +703,9 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
         if (sphi == 8) ((double*)hphi.data())[n] = v;
         else ((float*)hphi.data())[n] = (float)v;
     }
-    HIPCHK(hipMemcpyAsync(base + L.off_phi, hphi.data(), hphi.size(), hipMemcpyHostToDevice, s));
+    // (fused layout: in the second h buffer, which nothing else uses yet)
+    char* dphi = base + (L.fused ? L.off_h1 : L.off_phi);
+    HIPCHK(hipMemcpyAsync(dphi, hphi.data(), hphi.size(), hipMemcpyHostToDevice, s));
     double *du = nullptr, *dP = nullptr;
     if (init->u) {
         HIPCHK(hipMalloc(&du, (size_t)3 * N * sizeof(double)));
@@ -631,10 +716,11 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
         HIPCHK(hipMemcpyAsync(dP, init->P, (size_t)N * sizeof(double), hipMemcpyHostToDevice, s));
     }
     ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
-    InitIn in = {du, dP};
+    InitIn in = {du, dP, dphi};
     hipError_t e = launch_wall(p->storage, MODE_INIT, ddesc, (const WallRef*)(base + L.off_wrefs),
-                               (int)L.n_wall, s);
-    if (e == hipSuccess) e = launch_sweep(p->storage, phase_q(p), MODE_INIT, L.tx, 0, ddesc, dtiles, nt, 0, ro, in, s);
+                               (int)L.walls.size(), s);
+    if (e == hipSuccess) e = launch_sweep(p->storage, lq, MODE_INIT, L.tx, 0, ddesc, dtiles, nt, 0, ro, in, s);
+    if (e == hipSuccess && L.fused) e = hipMemsetAsync(base + L.off_h1, 0, L.h_bytes, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (du) hipFree(du);
     if (dP) hipFree(dP);
@@ -672,13 +758,14 @@ int read_lattice_staged(int storage, const Desc& hdesc, int parity, Desc* d_desc
     ro.P = (P && (mask & LBM_P)) ? buf + o_P : nullptr;
     ro.u = (u && (mask & LBM_U)) ? buf + o_u : nullptr;
     ro.pops = want_pop ? buf + o_pop : nullptr;
-    InitIn in = {nullptr, nullptr};
+    InitIn in = {nullptr, nullptr, nullptr};
+    const int lq = launch_q(hdesc);
     // nodes of dropped (all-solid) tiles are written by no read kernel: they
     // read 0 from the cleared staging
     hipError_t e = launch_fill_zero(buf, (int64_t)nd, s);
-    if (e == hipSuccess) e = launch_phi(storage, qh, parity, d_desc, d_tiles, ntiles, s, 1);
-    if (e == hipSuccess) e = launch_wall(storage, MODE_READ, d_desc, d_walls, nwalls, s);
-    if (e == hipSuccess) e = launch_sweep(storage, qh, MODE_READ, hdesc.tx, parity, d_desc, d_tiles, ntiles, 1, ro, in, s);
+    if (e == hipSuccess && !is_fused(lq)) e = launch_phi(storage, qh, parity, d_desc, d_tiles, ntiles, s, 1);
+    if (e == hipSuccess && !is_fused(lq)) e = launch_wall(storage, MODE_READ, d_desc, d_walls, nwalls, s);
+    if (e == hipSuccess) e = launch_sweep(storage, lq, MODE_READ, hdesc.tx, parity, d_desc, d_tiles, ntiles, 1, ro, in, s);
     if (e == hipSuccess && ro.phi) e = hipMemcpyAsync(phi, ro.phi, N * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && ro.P) e = hipMemcpyAsync(P, ro.P, N * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && ro.u) e = hipMemcpyAsync(u, ro.u, 3 * N * sizeof(double), hipMemcpyDeviceToHost, s);

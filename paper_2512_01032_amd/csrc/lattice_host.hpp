@@ -19,8 +19,9 @@ struct LatticeLayout {
     int tx = 64, ty = 4, tz = 16;
     int64_t N = 0;
     int64_t n_fluid = 0, n_ghost = 0, n_solid = 0;
-    int64_t n_wall = 0;           // near-wall fluid nodes (each has a slot)
-    size_t off_desc = 0, off_pop0 = 0, off_pop1 = 0, pop_bytes = 0, off_phi = 0, off_flag = 0,
+    int64_t n_wall = 0;           // near-wall fluid nodes
+    bool fused = false;           // in the fused layout (pflbm.hpp)
+    size_t off_desc = 0, off_pop0 = 0, off_pop1 = 0, pop_bytes = 0, off_h0 = 0, off_h1 = 0, h_bytes = 0, off_phi = 0, off_flag = 0,
            off_link = 0, off_tiles = 0, off_partials = 0, off_gbuf = 0, off_ghosts = 0,
            off_wslot = 0, off_hyst = 0, off_wall = 0, off_wgl = 0, off_wrefs = 0, off_wmat = 0,
            total = 0;
@@ -43,7 +44,7 @@ int validate_params(const lbm_params* p, const lbm_geometry* geo);
 
 // Tile width for a lattice of width nx; tile depth for a given tile count target.
 int choose_tx(int nx);
-int choose_tz(const lbm_params* p, int tx);
+int choose_tz(const lbm_params* p, int tx, bool fused);
 void xcd_order(std::vector<Tile>& t);   // XCD-aware launch order of a tile list
 
 // Size of the phase-field lattice (7 or 19).
@@ -55,9 +56,16 @@ void storage_sizes(int storage, int* sh, int* sg, int* sphi);
 // Sizes only (no geometry): used by lbm_footprint; assumes every tile is kept.
 size_t footprint_bytes(const lbm_params* p);
 
+// Launcher argument qp of a lattice.
+inline int launch_q(const Desc& d) {
+    return (d.q_phase == 19 ? 19 : 7) + (d.hb[0] ? QP_FUSED : 0);
+}
+
 // Full classification + tile table + offsets.  lat: lattice index stamped in
-// the tiles.  Returns LBM_OK or LBM_E_INVAL.
-int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, LatticeLayout* L);
+// the tiles.  fused: take the fused layout where the lattice allows it (it
+// needs more device memory than the separate-pass one).  Returns LBM_OK or
+// LBM_E_INVAL.
+int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fused, LatticeLayout* L);
 
 // Descriptor for device pointers rooted at base (device address of the arena).
 void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout& L,

@@ -53,7 +53,11 @@ extern "C" int lbm_create(const lbm_params* p, const lbm_geometry* geo, const lb
         memset(&h->geo, 0, sizeof(h->geo));
         for (int k = 0; k < 16; ++k) h->geo.theta_deg[k] = 90.0;
     }
-    int rc = build_layout(p, &h->geo, 0, &h->L);
+    // the fused layout where the memory allows it: it takes more than the
+    // separate passes' (within lbm_footprint but for narrow lattices)
+    int rc = build_layout(p, &h->geo, 0, true, &h->L);
+    if (rc == LBM_OK && h->L.fused && ctx && ctx->arena && ctx->arena_bytes < h->L.total)
+        rc = build_layout(p, &h->geo, 0, false, &h->L);
     if (rc != LBM_OK) { free_handle(h); return rc; }
     h->device = ctx ? ctx->device : 0;
     h->stream = ctx ? (hipStream_t)ctx->stream : nullptr;
@@ -73,7 +77,15 @@ extern "C" int lbm_create(const lbm_params* p, const lbm_geometry* geo, const lb
         h->base = (char*)ctx->arena;
     } else {
         e = hipMalloc((void**)&h->base, h->L.total);
+        if (e != hipSuccess && h->L.fused) {
+            (void)hipGetLastError();
+            h->base = nullptr;
+            rc = build_layout(p, &h->geo, 0, false, &h->L);
+            if (rc != LBM_OK) { free_handle(h); return rc; }
+            e = hipMalloc((void**)&h->base, h->L.total);
+        }
         if (e != hipSuccess) {
+            h->base = nullptr;
             set_error("hipMalloc(%zu): %s", h->L.total, hipGetErrorString(e));
             free_handle(h);
             return LBM_E_NOMEM;
@@ -92,7 +104,7 @@ extern "C" int lbm_create(const lbm_params* p, const lbm_geometry* geo, const lb
     h->dghosts = (GhostRef*)(h->base + h->L.off_ghosts);
     h->nghosts = (int)h->L.ghosts.size();
     h->dwalls = (WallRef*)(h->base + h->L.off_wrefs);
-    h->nwalls = (int)h->L.n_wall;
+    h->nwalls = (int)h->L.walls.size();
     h->step = h->hdesc.step;
     // the host copies of flags and links are no longer needed
     std::vector<uint8_t>().swap(h->L.flag);
@@ -133,15 +145,17 @@ static bool diag_step(const lbm_handle* h, int64_t t) {
     return de > 0 && (t % de) == 0;
 }
 
-// Queue the kernels of steps t0 .. t0+n-1 on stream s: per step the phi pass,
-// the wall pass, the sweep (its AA parity and diagnostic instance chosen by
-// the step), the pressure ghosts and the step counter.  With events (timed
-// runs) the phi + wall passes and the sweep kernel alone are bracketed.
+// Queue the kernels of steps t0 .. t0+n-1 on stream s: per step the sweep (its
+// AA parity and diagnostic instance chosen by the step) alone in the fused
+// layout; else the phi pass, the wall pass, the sweep, the pressure ghosts and
+// the step counter.  With events (timed runs) the phi + wall passes and the
+// sweep are bracketed.
 static int enqueue_steps(lbm_handle* h, int64_t t0, int64_t n, hipStream_t s, bool events) {
     const int storage = h->p.storage;
-    const int qp = phase_q(&h->p);
+    const bool fused = h->L.fused;
+    const int qp = launch_q(h->hdesc);
     const ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
-    const InitIn in = {nullptr, nullptr};
+    const InitIn in = {nullptr, nullptr, nullptr};
     for (int64_t k = 0; k < n; ++k) {
         const int64_t t = t0 + k;
         const int diag = diag_step(h, t) ? 1 : 0;
@@ -152,12 +166,13 @@ static int enqueue_steps(lbm_handle* h, int64_t t0, int64_t n, hipStream_t s, bo
             HIPRET(hipEventRecord(e0, s));
         }
         const int par = (int)(t & 1);
-        HIPRET(launch_phi(storage, qp, par, h->ddesc, h->dtiles, h->ntiles, s));
+        if (!fused) HIPRET(launch_phi(storage, qp, par, h->ddesc, h->dtiles, h->ntiles, s));
         if (h->nwalls) HIPRET(launch_wall(storage, MODE_STEP, h->ddesc, h->dwalls, h->nwalls, s));
         if (events) HIPRET(hipEventRecord(e1, s));
         HIPRET(launch_sweep(storage, qp, h->p.subvoxel ? MODE_STEP_SV : MODE_STEP, h->L.tx, par, h->ddesc,
                             h->dtiles, h->ntiles, diag, ro, in, s));
         if (events) HIPRET(hipEventRecord(e2, s));
+        if (fused) continue;
         if (h->nghosts) HIPRET(launch_ghosts(storage, qp, h->ddesc, h->dghosts, h->nghosts, s));
         HIPRET(launch_advance(h->ddesc, 1, s));
     }
@@ -196,20 +211,11 @@ static int capture_steps(lbm_handle* h, int par, int diag, int64_t n, hipGraphEx
     return LBM_OK;
 }
 
-static int ensure_graphs(lbm_handle* h) {
-    if (h->graphs_ready) return LBM_OK;
+// Capture the graph *g of n steps of this kind unless it is there already.
+static int ensure_graph(lbm_handle* h, int par, int diag, int64_t n, hipGraphExec_t* g) {
+    if (*g) return LBM_OK;
     if (!h->cap_stream) HIPRET(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-    for (int par = 0; par < 2; ++par) {
-        for (int diag = 0; diag < 2; ++diag) {
-            if (diag && h->p.diag_every <= 0) continue;
-            int rc = capture_steps(h, par, diag, 1, &h->one[par][diag]);
-            if (rc != LBM_OK) return rc;
-        }
-        int rc = capture_steps(h, par, 0, GRAPH_CHUNK, &h->chunk[par]);
-        if (rc != LBM_OK) return rc;
-    }
-    h->graphs_ready = true;
-    return LBM_OK;
+    return capture_steps(h, par, diag, n, g);
 }
 
 extern "C" int lbm_step(lbm_handle* h, int64_t nsteps) {
@@ -227,21 +233,25 @@ extern "C" int lbm_step(lbm_handle* h, int64_t nsteps) {
         rc = enqueue_steps(h, h->step, nsteps, h->stream, true);
         if (rc != LBM_OK) return rc;
     } else {
-        rc = ensure_graphs(h);
-        if (rc != LBM_OK) return rc;
         int64_t k = 0;
         while (k < nsteps) {
             const int64_t t = h->step + k;
-            const int par = (int)(t & 1);
-            bool chunk_ok = h->chunk[par] && nsteps - k >= GRAPH_CHUNK;
-            if (chunk_ok && de > 0) {
-                const int64_t next_diag = ((t + de - 1) / de) * de;
-                chunk_ok = next_diag >= t + GRAPH_CHUNK;
+            const int par = (int)(t & 1), diag = diag_step(h, t) ? 1 : 0;
+            bool chunk = nsteps - k >= GRAPH_CHUNK;
+            if (chunk && de > 0) chunk = ((t + de - 1) / de) * de >= t + GRAPH_CHUNK;
+            const int64_t n = chunk ? GRAPH_CHUNK : 1;
+            if (!chunk && h->L.fused) {
+                // a single step is one kernel: launched as it is
+                rc = enqueue_steps(h, t, n, h->stream, false);
+                if (rc != LBM_OK) return rc;
+            } else {
+                hipGraphExec_t* g = chunk ? &h->chunk[par] : &h->one[par][diag];
+                rc = ensure_graph(h, par, diag, n, g);
+                if (rc != LBM_OK) return rc;
+                if (!*g) { set_error("no step graph for step %lld", (long long)t); return LBM_E_STATE; }
+                HIPRET(hipGraphLaunch(*g, h->stream));
             }
-            hipGraphExec_t g = chunk_ok ? h->chunk[par] : h->one[par][diag_step(h, t) ? 1 : 0];
-            if (!g) { set_error("no step graph for step %lld", (long long)t); return LBM_E_STATE; }
-            HIPRET(hipGraphLaunch(g, h->stream));
-            k += chunk_ok ? GRAPH_CHUNK : 1;
+            k += n;
         }
     }
     h->step += nsteps;

@@ -6,7 +6,10 @@
 //   phi [N]     order parameter of the current step (written by the phi pass)
 //   flag[N]     node kind / material / face / near-wall / ghost-owner bits
 //   link[N]     per-node solid-link mask and owned pressure faces
-// and is swept in tiles of TX x TY = 256 columns marching over a z-chunk.
+// and is swept in tiles of TX x TY = 256 columns over a z-chunk.  That is the
+// separate-pass layout.  In the fused layout (one kernel per step) g keeps the
+// blocked form alone, h has two buffers in blocks of one tile width (Desc::hb),
+// and phi is not stored.
 // Several lattices (serving) share one tile table; every tile names its
 // lattice, and each lattice's descriptor carries its own parameters, step
 // counter and parity.
@@ -69,6 +72,7 @@ __host__ __device__ constexpr PopLayout pop_layout(int qp, int sh, int sg) {
     if (tot <= 104) return PopLayout{1, qp + 19, tot};
     int k = 1;
     while (2 * pop_prefix(k, qp, sh, sg) < tot) ++k;
+    if (qp == 0) k += 1 - k % 2;   // g alone: no pair (i, opp(i)) across the cut
     const int a = pop_prefix(k, qp, sh, sg);
     return PopLayout{2, k, a > tot - a ? a : tot - a};
 }
@@ -113,7 +117,14 @@ struct alignas(256) Desc {
                                    // rows 0-17 the wall fraction q of links 1-18, rows
                                    // 18-20 the unit wall normal into the fluid
     int32_t subvoxel;              // 1: interpolated bounce-back of g at the wall fractions
-    int32_t pad_sv;
+    // fused layout: the h entering step t are in hb[t & 1], in rows (y, z) of nxh
+    // nodes cut into blocks of tx nodes: direction i of a block is its tx entries
+    // from i tx on
+    void* hb[2];                   // (NULL: separate passes)
+    int32_t nxh, pad_nxh;          // row length of h, nx padded to the tile width
+    int64_t hbytes;                // of one buffer
+    int64_t step2[2];              // fused layout: the step counter read by the sweep of each
+                                   // parity, which writes the other entry for the next step
     // time
     int64_t step;                  // advanced on the device after each step's ghost pass
     int64_t t0;                    // step counter value at physical time 0
@@ -140,7 +151,6 @@ struct alignas(256) Desc {
     double pd[32];
     // outputs of the last diagnostic reduction
     double diag[NPART];
-    int64_t diag_step;
     int32_t unstable;              // sticky: NaN or |u| > u_max seen
     int32_t pad1;
 };
@@ -161,6 +171,10 @@ constexpr int MODE_STEP = 0;   // stream + collide, AA in place
 constexpr int MODE_READ = 1;   // macroscopic fields / populations to output buffers
 constexpr int MODE_INIT = 2;   // equilibria from (phi, u, P) into even-parity slots
 constexpr int MODE_STEP_SV = 3;  // launcher mode: MODE_STEP with sub-voxel walls enabled
+
+// Launcher argument qp: the phase-lattice size, plus QP_FUSED in the fused layout.
+constexpr int QP_FUSED = 256;
+inline bool is_fused(int qp) { return qp >= QP_FUSED; }
 
 struct GhostRef {              // one pressure ghost: lattice and node
     int32_t lat;
@@ -193,11 +207,14 @@ struct ReadOut {               // device buffers of MODE_READ (NULL: skip)
 struct InitIn {                // device inputs of MODE_INIT
     const double* u;           // [3][N] or NULL
     const double* P;           // [N] or NULL
+    const void* phi;           // [N] (compute type), ghosts filled (fused layout only)
 };
 
 // host-side launchers (kernels.hip).  qp: phase-lattice size (7 or 19) of
 // every lattice in the table; parity: AA parity of the step every lattice
-// in the table is at; tx: tile width of every tile (16, 32 or 64).
+// in the table is at; tx: tile width of every tile (16, 32 or 64).  In
+// the fused layout the sweep is the whole step, and no other launch goes with
+// it.
 // force: run the phi pass even for lattices past their stop step (read-back).
 hipError_t launch_phi(int storage, int qp, int parity, const Desc* d, const Tile* tiles, int ntiles,
                       hipStream_t s, int force = 0);

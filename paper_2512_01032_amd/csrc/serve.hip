@@ -291,7 +291,7 @@ int read_back(lbm_server* s) {
             const Tile* dt = (const Tile*)(s->arena + job->off + job->L.off_tiles);
             const WallRef* dw = (const WallRef*)(s->arena + job->off + job->L.off_wrefs);
             rc = read_lattice_staged(s->cfg.storage, job->hdesc, (int)(job->nsteps & 1), dd, dt,
-                                     (int)job->L.tiles.size(), dw, (int)job->L.n_wall, mask, job->phi,
+                                     (int)job->L.tiles.size(), dw, (int)job->L.walls.size(), mask, job->phi,
                                      job->P, job->u, nullptr, s->dstage, s->up_stream);
             double v[NPART];
             if (rc == LBM_OK) {
@@ -355,7 +355,8 @@ int rebuild_tables(lbm_server* s) {
     s->groups.clear();
     s->phi_groups.clear();
     s->ghost_groups.clear();
-    for (int qp : {7, 19}) {
+    auto lattice_q = [](const Job& j) { return launch_q(j.hdesc); };
+    for (int qp : {QP_FUSED + 7, 7, 19}) {
         const int qoff = (int)tiles.size();
         for (int tx : {64, 32, 16}) {
             // lattices with sub-voxel walls run their own instance of the
@@ -364,16 +365,16 @@ int rebuild_tables(lbm_server* s) {
             for (int sv : {0, 1}) {
                 const int off = (int)tiles.size();
                 for (auto& j : s->active) {
-                    if (j->L.tx != tx || phase_q(&j->p) != qp || (j->p.subvoxel ? 1 : 0) != sv) continue;
+                    if (j->L.tx != tx || lattice_q(*j) != qp || (j->p.subvoxel ? 1 : 0) != sv) continue;
                     for (Tile t : j->L.tiles) { t.lat = j->slot; tiles.push_back(t); }
                 }
                 if ((int)tiles.size() > off) s->groups.push_back({qp, tx, off, (int)tiles.size() - off, sv});
             }
         }
-        if ((int)tiles.size() > qoff) s->phi_groups.push_back({qp, 0, qoff, (int)tiles.size() - qoff});
+        if (!is_fused(qp) && (int)tiles.size() > qoff) s->phi_groups.push_back({qp, 0, qoff, (int)tiles.size() - qoff});
         const int goff = (int)ghosts.size();
         for (auto& j : s->active) {
-            if (phase_q(&j->p) != qp) continue;
+            if (lattice_q(*j) != qp || is_fused(qp)) continue;
             for (GhostRef g : j->L.ghosts) { g.lat = j->slot; ghosts.push_back(g); }
         }
         if ((int)ghosts.size() > goff)
@@ -384,10 +385,11 @@ int rebuild_tables(lbm_server* s) {
         // the wall pass takes its lattice constants per block: pad each
         // lattice's list to whole blocks (node -1 is skipped)
         while (walls.size() % NTHREADS) walls.push_back(WallRef{j->slot, -1, 0, 0u});
-        s->hslots.push_back(j->slot);
+        // (the step kernel advances its lattices' step counters)
+        if (!j->L.fused) s->hslots.push_back(j->slot);
     }
     s->nmirror = 0;
-    for (int sl : s->hslots) s->nmirror = std::max(s->nmirror, sl + 1);
+    for (auto& j : s->active) s->nmirror = std::max(s->nmirror, j->slot + 1);
     int rc = upload_table(&s->dwalls, &s->walls_cap, walls, s->stream);
     if (rc == LBM_OK) rc = upload_table(&s->dtiles, &s->tiles_cap, tiles, s->stream);
     if (rc == LBM_OK) rc = upload_table(&s->dghosts, &s->ghosts_cap, ghosts, s->stream);
@@ -405,7 +407,7 @@ int rebuild_tables(lbm_server* s) {
 hipError_t enqueue_steps(lbm_server* s, hipStream_t st) {
     const int storage = s->cfg.storage;
     const ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
-    const InitIn in = {nullptr, nullptr};
+    const InitIn in = {nullptr, nullptr, nullptr};
     for (int k = 0; k < s->interval; ++k) {
         const int par = k & 1;
         hipError_t e = hipSuccess;
@@ -502,9 +504,11 @@ void worker_main(lbm_server* s) {
             for (size_t k = 0; k < s->active.size();) {
                 Job* j = s->active[k].get();
                 j->step = std::min(j->step + s->interval, j->nsteps);
-                if (s->hmirror[j->slot].step != j->step) {
+                // an interval ends at an even parity
+                const int64_t at = j->L.fused ? s->hmirror[j->slot].step2[0] : s->hmirror[j->slot].step;
+                if (at != j->step) {
                     set_error("lattice in slot %d is at step %lld, expected %lld", j->slot,
-                              (long long)s->hmirror[j->slot].step, (long long)j->step);
+                              (long long)at, (long long)j->step);
                     rc = LBM_E_STATE;
                     break;
                 }
@@ -629,7 +633,9 @@ extern "C" int lbm_submit(lbm_server* s, const lbm_request* req, uint64_t* ticke
     job->geo.sdf = job->sdf.empty() ? nullptr : job->sdf.data();
     // node classification, tile table and arena layout on the caller's
     // thread: the worker only uploads
-    rc = build_layout(&job->p, &job->geo, 0, &job->L);
+    rc = build_layout(&job->p, &job->geo, 0, true, &job->L);
+    if (rc == LBM_OK && job->L.fused && job->L.total > s->arena_bytes)
+        rc = build_layout(&job->p, &job->geo, 0, false, &job->L);   // the smaller layout
     if (rc != LBM_OK) return rc;
     job->bytes = job->L.total;
     job->nsteps = req->nsteps;
