@@ -88,9 +88,11 @@ int read_lattice(int storage, const Desc& hdesc, int parity, Desc* d_desc, const
 size_t read_staging_elems(const Desc& hdesc, uint32_t mask, const double* phi, const double* P,
                           const double* u, const double* pops);
 // read_lattice with caller-provided device staging buf of at least
-// read_staging_elems() doubles: allocates nothing.  Synchronous.
+// read_staging_elems() doubles, and pinned host memory pin of COPY_PIN_BYTES for
+// the copies (NULL: plain copies): allocates nothing.  Synchronous.
+constexpr size_t COPY_PIN_BYTES = (size_t)16 << 20;
 int read_lattice_staged(int storage, const Desc& hdesc, int parity, Desc* d_desc, const Tile* d_tiles,
                         int ntiles, const WallRef* d_walls, int nwalls, uint32_t mask, double* phi,
-                        double* P, double* u, double* pops, double* buf, hipStream_t s);
+                        double* P, double* u, double* pops, double* buf, char* pin, hipStream_t s);
 
 }  // namespace pflbm

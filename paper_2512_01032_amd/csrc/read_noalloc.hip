@@ -63,5 +63,5 @@ extern "C" int lbm_read_fields_noalloc(lbm_handle* h, uint32_t mask, double* phi
     e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) { set_error("hipStreamSynchronize: %s", hipGetErrorString(e)); return LBM_E_DEVICE; }
     return read_lattice_staged(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->dtiles,
-                               h->ntiles, h->dwalls, h->nwalls, mask, phi, P, u, pops, buf, h->stream);
+                               h->ntiles, h->dwalls, h->nwalls, mask, phi, P, u, pops, buf, nullptr, h->stream);
 }

@@ -148,6 +148,7 @@ struct lbm_server {
     // read-back staging (device), grown on demand
     double* dstage = nullptr;
     size_t stage_cap = 0;
+    char* hpin = nullptr;              // pinned memory of the read-backs' copies
     // jobs
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -287,12 +288,16 @@ int read_back(lbm_server* s) {
                 s->stage_cap = std::max(nd, 2 * s->stage_cap);
                 SRV_CHK(hipMalloc(&s->dstage, s->stage_cap * sizeof(double)));
             }
+            if (!s->hpin && hipHostMalloc((void**)&s->hpin, COPY_PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+                (void)hipGetLastError();
+                s->hpin = nullptr;
+            }
             Desc* dd = s->dtable + job->slot;
             const Tile* dt = (const Tile*)(s->arena + job->off + job->L.off_tiles);
             const WallRef* dw = (const WallRef*)(s->arena + job->off + job->L.off_wrefs);
             rc = read_lattice_staged(s->cfg.storage, job->hdesc, (int)(job->nsteps & 1), dd, dt,
                                      (int)job->L.tiles.size(), dw, (int)job->L.walls.size(), mask, job->phi,
-                                     job->P, job->u, nullptr, s->dstage, s->up_stream);
+                                     job->P, job->u, nullptr, s->dstage, s->hpin, s->up_stream);
             double v[NPART];
             if (rc == LBM_OK) {
                 hipError_t e = hipMemcpyAsync(v, dd->diag, sizeof(v), hipMemcpyDeviceToHost, s->up_stream);
@@ -711,6 +716,7 @@ extern "C" int lbm_server_destroy(lbm_server* s) {
     if (s->dwalls) hipFree(s->dwalls);
     if (s->dslots) hipFree(s->dslots);
     if (s->dstage) hipFree(s->dstage);
+    if (s->hpin) hipHostFree(s->hpin);
     if (s->up_stream) { hipStreamSynchronize(s->up_stream); hipStreamDestroy(s->up_stream); }
     if (s->cap_stream) hipStreamDestroy(s->cap_stream);
     if (s->ev) hipEventDestroy(s->ev);
