@@ -617,15 +617,15 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     int sh, sg, sphi;
     storage_sizes(p->storage, &sh, &sg, &sphi);
     // zero populations and phi (solid slots stay zero), upload geometry
-    HIPCHK(hipMemsetAsync(base + L.off_pop0, 0, L.pop_bytes, s));
-    if (L.off_pop1 != L.off_pop0) HIPCHK(hipMemsetAsync(base + L.off_pop1, 0, L.pop_bytes, s));
+    if (L.fused) {
+        HIPCHK(hipMemsetAsync(base + L.off_pop0, 0, L.off_h1 + L.h_bytes - L.off_pop0, s));
+    } else {
+        HIPCHK(hipMemsetAsync(base + L.off_pop0, 0, L.pop_bytes, s));
+        if (L.off_pop1 != L.off_pop0) HIPCHK(hipMemsetAsync(base + L.off_pop1, 0, L.pop_bytes, s));
+    }
     HIPCHK(hipMemsetAsync(base + L.off_partials, 0, L.tiles.size() * NPART * sizeof(double), s));
     HIPCHK(hipMemcpyAsync(base + L.off_flag, L.flag.data(), N, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(base + L.off_link, L.link.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
-    if (L.fused) {
-        HIPCHK(hipMemsetAsync(base + L.off_h0, 0, L.h_bytes, s));
-        HIPCHK(hipMemsetAsync(base + L.off_h1, 0, L.h_bytes, s));
-    }
     if (!L.wslot.empty())
         HIPCHK(hipMemcpyAsync(base + L.off_wslot, L.wslot.data(), (size_t)N * 4, hipMemcpyHostToDevice, s));
     if (!L.walls.empty()) {
@@ -705,7 +705,7 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
         if (sphi == 8) ((double*)hphi.data())[n] = v;
         else ((float*)hphi.data())[n] = (float)v;
     }
-    // (fused layout: in the second h buffer, which nothing else uses yet)
+    // (fused layout: in the second h buffer, whose live entries step 0 writes)
     char* dphi = base + (L.fused ? L.off_h1 : L.off_phi);
     HIPCHK(hipMemcpyAsync(dphi, hphi.data(), hphi.size(), hipMemcpyHostToDevice, s));
     double *du = nullptr, *dP = nullptr;
@@ -722,7 +722,6 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     hipError_t e = launch_wall(p->storage, MODE_INIT, ddesc, (const WallRef*)(base + L.off_wrefs),
                                (int)L.walls.size(), s);
     if (e == hipSuccess) e = launch_sweep(p->storage, lq, MODE_INIT, L.tx, 0, ddesc, dtiles, nt, 0, ro, in, s);
-    if (e == hipSuccess && L.fused) e = hipMemsetAsync(base + L.off_h1, 0, L.h_bytes, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (du) hipFree(du);
     if (dP) hipFree(dP);

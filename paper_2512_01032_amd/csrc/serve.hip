@@ -409,29 +409,39 @@ int rebuild_tables(lbm_server* s) {
 }
 
 // The launches of one interval (every step starts at the parity of its index).
+// A group in the fused layout needs nothing of the others, so it takes its steps
+// of the interval one after another: its populations stay in the Infinity Cache
+// where those of all groups would not (twelve droplets and channels of 32 to 96
+// nodes a side, 420 MB in three groups: 91.2 -> 79.4 ms; cut further, into
+// batches of at most 96, 160 or 224 MB: 82.5, 82.2, 81.1).
 hipError_t enqueue_steps(lbm_server* s, hipStream_t st) {
     const int storage = s->cfg.storage;
     const ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
     const InitIn in = {nullptr, nullptr, nullptr};
-    for (int k = 0; k < s->interval; ++k) {
+    hipError_t e = hipSuccess;
+    auto sweep = [&](const lbm_server::Group& g, int par) {
+        if (e == hipSuccess)
+            e = launch_sweep(storage, g.qp, g.sv ? MODE_STEP_SV : MODE_STEP, g.tx, par, s->dtable,
+                             s->dtiles + g.off, g.n, 0, ro, in, st);
+    };
+    for (int k = 0; s->nslots > 0 && k < s->interval; ++k) {
         const int par = k & 1;
-        hipError_t e = hipSuccess;
         for (const auto& g : s->phi_groups)
             if (e == hipSuccess)
                 e = launch_phi(storage, g.qp, par, s->dtable, s->dtiles + g.off, g.n, st, 0);
         if (e == hipSuccess && s->nwalls)
             e = launch_wall(storage, MODE_STEP, s->dtable, s->dwalls, s->nwalls, st);
         for (const auto& g : s->groups)
-            if (e == hipSuccess)
-                e = launch_sweep(storage, g.qp, g.sv ? MODE_STEP_SV : MODE_STEP, g.tx, par, s->dtable,
-                                 s->dtiles + g.off, g.n, 0, ro, in, st);
+            if (!is_fused(g.qp)) sweep(g, par);
         for (const auto& g : s->ghost_groups)
             if (e == hipSuccess)
                 e = launch_ghosts(storage, g.qp, s->dtable, s->dghosts + g.off, g.n, st);
         if (e == hipSuccess) e = launch_advance_list(s->dtable, s->dslots, s->nslots, st);
-        if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    for (const auto& g : s->groups)
+        if (is_fused(g.qp))
+            for (int k = 0; k < s->interval; ++k) sweep(g, k & 1);
+    return e;
 }
 
 // Queue one interval of the current tables and the copy of the table's step
