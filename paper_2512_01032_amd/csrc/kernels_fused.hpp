@@ -394,13 +394,14 @@ __device__ inline void f_phase_eq(const FNode<T>& n, const Phys<T>& ph, const SE
     }
 }
 
-// FP64 diagnostics of one node into the thread's partials.
+// FP64 diagnostics of one node into the thread's partials (max |u| as its square:
+// the root is monotone and taken once per tile).
 template <typename T>
 __device__ inline void f_diag(double* acc, const FNode<T>& n, const Phys<T>& ph) {
     const T pc = n.pc;
-    const double um = sqrt((double)n.uu);
+    const double uu = (double)n.uu;
     const double P = (double)(T(TGc) * (ph[PI_GREF] + n.pdev));
-    if (isnan((double)pc) || isnan(um) || isnan(P)) {
+    if (isnan((double)pc) || isnan(uu) || isnan(P)) {
         acc[P_NAN] += 1.0;
         return;
     }
@@ -408,7 +409,7 @@ __device__ inline void f_diag(double* acc, const FNode<T>& n, const Phys<T>& ph)
     acc[P_MX] += (double)(n.rho * n.u[0]);
     acc[P_MY] += (double)(n.rho * n.u[1]);
     acc[P_MZ] += (double)(n.rho * n.u[2]);
-    acc[P_UMAX] = fmax(acc[P_UMAX], um);
+    acc[P_UMAX] = fmax(acc[P_UMAX], uu);
     if (pc > T(0.99)) { acc[P_PLIQ] += P; acc[P_NLIQ] += 1.0; }
     if (pc < T(0.01)) { acc[P_PGAS] += P; acc[P_NGAS] += 1.0; }
 }
@@ -534,7 +535,7 @@ __device__ inline void feed_ghosts(const Desc* D, const GB& gb, const HR& hn, co
 // waits).
 template <typename T, typename SH, typename SG, int MODE, bool DIAG, int TX, int PAR>
 __global__ void __launch_bounds__(NTHREADS)
-step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut ro, InitIn in) {
+step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, bool back, ReadOut ro, InitIn in) {
     static_assert(!Store<SH>::scaled, "h is stored unscaled");
     constexpr int QP = QH, TY = NTHREADS / TX, WAVES = NTHREADS / 64;
     constexpr int LW = TX + 2, LN = (TX + 2) * (TY + 2);
@@ -545,9 +546,10 @@ step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut ro
     __shared__ uint8_t s_wlist[NTHREADS];     // their threads, one segment per wave
     __shared__ int s_wcnt[WAVES];
     __shared__ T s_cs[2][16];                 // cos and sin of each material's contact angle
-    __shared__ double s_red[DIAG ? NPART : 1][WAVES];
+    __shared__ double s_acc[DIAG ? 7 : 1][DIAG ? NTHREADS : 1];
+    __shared__ int s_cnt[3][WAVES];
 
-    const Tile tl = load_tile(tiles);
+    const Tile tl = load_tile(tiles, back);
     Desc* D = descs + tl.lat;
     const int tid = threadIdx.x;
     const int64_t step = uni(D->step2[PAR]);
@@ -844,16 +846,38 @@ step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut ro
     }
     if constexpr (DIAG && MODE != MODE_INIT) {
         if (!diag) return;
+        // Counts are ballots.  The other seven quantities go through LDS, so that a
+        // wave sums one or two of them over the tile's 256 nodes: a tree per wave
+        // and quantity exchanged seven times as much and bound the pass
+        // (lbm_reduce, FP16 g duct 256 x 256 x 512, 803 us).
+        constexpr int NSUM = 7;
+        const int lane = tid & 63, w = uni(tid >> 6);
+        auto part = [](int j) -> int { return j < P_PLIQ - 1 ? j : (j == P_PLIQ - 1 ? P_PLIQ : P_PGAS); };
 #pragma unroll
-        for (int j = 0; j < NPART; ++j) {
-            const double v = (j == P_UMAX) ? wave_max(acc[j]) : wave_sum(acc[j]);
-            if ((tid & 63) == 0) s_red[j][tid >> 6] = v;
+        for (int j = 0; j < NSUM; ++j) s_acc[j][tid] = acc[part(j)];
+        constexpr int CNT[3] = {P_NAN, P_NLIQ, P_NGAS};
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(acc[CNT[j]] > 0.0);
+            if (lane == 0) s_cnt[j][w] = __builtin_popcountll(m);
         }
-        __syncthreads();
-        if (tid < NPART) {
-            double v = s_red[tid][0];
-            for (int w = 1; w < WAVES; ++w) v = (tid == P_UMAX) ? fmax(v, s_red[tid][w]) : v + s_red[tid][w];
-            D->partials[(int64_t)tid * uni(D->ntiles) + tl.tile_in_lat] = v;
+        lds_barrier();
+        double* __restrict__ out = D->partials + tl.tile_in_lat;
+        const int64_t nt = uni(D->ntiles);
+        for (int j = w; j < NSUM; j += WAVES) {
+            double v = s_acc[j][lane];
+#pragma unroll
+            for (int k = 1; k < WAVES; ++k) {
+                const double o = s_acc[j][lane + 64 * k];
+                v = j == P_UMAX ? fmax(v, o) : v + o;
+            }
+            v = j == P_UMAX ? sqrt(wave_max(v)) : wave_sum(v);
+            if (lane == 0) out[part(j) * nt] = v;
+        }
+        if (tid < 3) {
+            int c = 0;
+            for (int k = 0; k < WAVES; ++k) c += s_cnt[tid][k];
+            out[(tid == 0 ? P_NAN : (tid == 1 ? P_NLIQ : P_NGAS)) * nt] = (double)c;
         }
     }
 }
@@ -898,20 +922,20 @@ fused_restore_kernel(const Desc* __restrict__ descs, const Tile* __restrict__ ti
 
 // ---------------------------------------------------------------- launchers
 template <typename T, typename SH, typename SG, int TX, int PAR>
-hipError_t launch_step_tp(int mode, Desc* d, const Tile* tiles, int ntiles, int diag, ReadOut ro, InitIn in,
+hipError_t launch_step_tp(bool back, int mode, Desc* d, const Tile* tiles, int ntiles, int diag, ReadOut ro, InitIn in,
                           hipStream_t s) {
     dim3 grid(ntiles), block(NTHREADS);
     switch (mode) {
         case MODE_STEP:
-            if (diag) step_kernel<T, SH, SG, MODE_STEP, true, TX, PAR><<<grid, block, 0, s>>>(d, tiles, ro, in);
-            else step_kernel<T, SH, SG, MODE_STEP, false, TX, PAR><<<grid, block, 0, s>>>(d, tiles, ro, in);
+            if (diag) step_kernel<T, SH, SG, MODE_STEP, true, TX, PAR><<<grid, block, 0, s>>>(d, tiles, back, ro, in);
+            else step_kernel<T, SH, SG, MODE_STEP, false, TX, PAR><<<grid, block, 0, s>>>(d, tiles, back, ro, in);
             break;
         case MODE_READ:
-            step_kernel<T, SH, SG, MODE_READ, true, TX, PAR><<<grid, block, 0, s>>>(d, tiles, ro, in);
+            step_kernel<T, SH, SG, MODE_READ, true, TX, PAR><<<grid, block, 0, s>>>(d, tiles, back, ro, in);
             break;
         case MODE_INIT:
             // (a lattice starts at step 0)
-            if constexpr (PAR == 0) step_kernel<T, SH, SG, MODE_INIT, false, TX, 0><<<grid, block, 0, s>>>(d, tiles, ro, in);
+            if constexpr (PAR == 0) step_kernel<T, SH, SG, MODE_INIT, false, TX, 0><<<grid, block, 0, s>>>(d, tiles, back, ro, in);
             else return hipErrorInvalidValue;
             break;
         default:
@@ -920,16 +944,17 @@ hipError_t launch_step_tp(int mode, Desc* d, const Tile* tiles, int ntiles, int 
     return hipGetLastError();
 }
 
+// back: the tile list backwards
 template <typename T, typename SH, typename SG>
-hipError_t launch_step(int mode, int tx, int parity, Desc* d, const Tile* tiles, int ntiles, int diag, ReadOut ro,
+hipError_t launch_step(bool back, int mode, int tx, int parity, Desc* d, const Tile* tiles, int ntiles, int diag, ReadOut ro,
                        InitIn in, hipStream_t s) {
     switch (tx * 2 + (parity & 1)) {
-        case 128: return launch_step_tp<T, SH, SG, 64, 0>(mode, d, tiles, ntiles, diag, ro, in, s);
-        case 129: return launch_step_tp<T, SH, SG, 64, 1>(mode, d, tiles, ntiles, diag, ro, in, s);
-        case 64: return launch_step_tp<T, SH, SG, 32, 0>(mode, d, tiles, ntiles, diag, ro, in, s);
-        case 65: return launch_step_tp<T, SH, SG, 32, 1>(mode, d, tiles, ntiles, diag, ro, in, s);
-        case 32: return launch_step_tp<T, SH, SG, 16, 0>(mode, d, tiles, ntiles, diag, ro, in, s);
-        case 33: return launch_step_tp<T, SH, SG, 16, 1>(mode, d, tiles, ntiles, diag, ro, in, s);
+        case 128: return launch_step_tp<T, SH, SG, 64, 0>(back, mode, d, tiles, ntiles, diag, ro, in, s);
+        case 129: return launch_step_tp<T, SH, SG, 64, 1>(back, mode, d, tiles, ntiles, diag, ro, in, s);
+        case 64: return launch_step_tp<T, SH, SG, 32, 0>(back, mode, d, tiles, ntiles, diag, ro, in, s);
+        case 65: return launch_step_tp<T, SH, SG, 32, 1>(back, mode, d, tiles, ntiles, diag, ro, in, s);
+        case 32: return launch_step_tp<T, SH, SG, 16, 0>(back, mode, d, tiles, ntiles, diag, ro, in, s);
+        case 33: return launch_step_tp<T, SH, SG, 16, 1>(back, mode, d, tiles, ntiles, diag, ro, in, s);
     }
     return hipErrorInvalidValue;
 }

@@ -1477,7 +1477,7 @@ template <typename T, typename SH, typename SG>
 hipError_t launch_sweep_storage(int qp, int mode, int tx, int parity, Desc* d, const Tile* tiles,
                                 int ntiles, int diag, ReadOut ro, InitIn in, hipStream_t s) {
     if (ntiles <= 0) return hipSuccess;
-    if (is_fused(qp)) return launch_step<T, SH, SG>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
+    if (is_fused(qp)) return launch_step<T, SH, SG>(qp >= QP_BACK && (parity & 1), mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
     if (qp == 19) return launch_sweep_q<T, SH, SG, 19>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
     return launch_sweep_q<T, SH, SG, QH>(mode, tx, parity, d, tiles, ntiles, diag, ro, in, s);
 }

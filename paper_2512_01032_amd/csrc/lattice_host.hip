@@ -195,6 +195,33 @@ void xcd_order(std::vector<Tile>& t) {
     t.swap(o);
 }
 
+// The order of lattices beyond the Infinity Cache: the XCDs walk the z-planes
+// together, each its eighth of a plane's rows.  Their reads and writes then stay
+// within a few planes of HBM at a time instead of eight distant slabs, a plane's
+// neighbours are still in the Infinity Cache whichever XCD used them last, and an
+// XCD meets its own rows again in the next plane.
+void plane_order(std::vector<Tile>& t) {
+    constexpr size_t NX = 8;
+    std::vector<Tile> q[NX], o;
+    o.reserve(t.size());
+    size_t extra = 0;   // the longer parts go round the XCDs
+    for (size_t i = 0, j; i < t.size(); i = j) {
+        for (j = i; j < t.size() && t[j].z0 == t[i].z0;) ++j;
+        const size_t m = j - i;
+        size_t at = i;
+        for (size_t k = 0; k < NX; ++k) {
+            const size_t c = m / NX + ((k + NX - extra % NX) % NX < m % NX ? 1 : 0);
+            q[k].insert(q[k].end(), t.begin() + at, t.begin() + at + c);
+            at += c;
+        }
+        extra += m % NX;
+    }
+    for (size_t r = 0; o.size() < t.size(); ++r)
+        for (size_t k = 0; k < NX; ++k)
+            if (r < q[k].size()) o.push_back(q[k][r]);
+    t.swap(o);
+}
+
 static void face_planes(const lbm_params* p, LatticeLayout* L) {
     int64_t b = 0;
     for (int f = 0; f < 6; ++f) {
@@ -220,24 +247,37 @@ static int64_t g_group_bytes(const lbm_params* p) {
     return (int64_t)pad_row(p->nx) * p->ny * p->nz * pop_layout(0, sg, sg).pb;
 }
 // Whether a lattice takes the fused layout (one kernel per step): D3Q7 phase
-// lattice, whole-voxel walls, and populations (two h buffers and g) of at most
-// 512 MB, so that those of its non-solid tiles live in the 256 MB Infinity Cache
-// from step to step or nearly so.  us per step of an n x n x 2n constricted duct
-// (30 % solid), separate passes / fused:
-//   FP32    n = 64: 40.2 / 22.7    96: 82.0 / 53.8   112: 134.6 / 134.4   160: 301 / 322   256: 1060 / 1127
-//   FP64    n = 64: 61.9 / 49.2    80: 90.3 / 67.1    96: 142.9 / 140.2   128: 304 / 314
-//   FP16 g  n = 64: 38.6 / 20.2    96: 75.4 / 47.8   128: 125.0 / 125.1   160: 251 / 259   256:  781 /  825
-// (n = 112, 96 and 128 hold 371, 467 and 394 MB).  Beyond, HBM bounds both: an
-// update in place runs at 5.9 TB/s and a copy at 4.8, and the fused step moves h
-// from one buffer to the other.
-constexpr int64_t FUSED_MAX_BYTES = (int64_t)512 << 20;
+// lattice, whole-voxel walls, FP64 ones only up to 750 MB of populations (two h
+// buffers and g), and 32-bit offsets.  us per step of an n x n x 2n constricted
+// duct (30 % solid), separate passes / fused:
+//   FP32    n = 64: 40.2 / 22.7    96: 82.0 / 53.8   128: 151 / 133   192: 555 / 450   256: 1080 / 1027
+//   FP64    n = 64: 61.9 / 49.2    80: 90.3 / 67.1    96: 143 / 137   112: 233 / 209   128:  304 /  302
+//   FP16 g  n = 64: 38.6 / 20.2    96: 75.4 / 47.8   128: 125 / 116   192: 416 / 364   256:  781 /  755
+// While the populations stay in the 256 MB Infinity Cache the separate passes are
+// bound by their launches; beyond, by HBM, where the phi pass' second look at h
+// costs more than the second h buffer.
+static int64_t fused_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
+}
 static bool fits_fused(const lbm_params* p) {
     if (phase_q(p) != QH || p->subvoxel) return false;
     if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
-    int sh, sg, sphi;
-    storage_sizes(p->storage, &sh, &sg, &sphi);
-    return 2 * h_buffer_bytes(p) + pop_layout(0, sg, sg).G * g_group_bytes(p) <= FUSED_MAX_BYTES;
+    if (p->storage == ST_FP64 && fused_bytes(p) > (int64_t)750 * 1000 * 1000) return false;
+    const int64_t lim = (int64_t)1 << 32;
+    return h_buffer_bytes(p) < lim && g_group_bytes(p) < lim;
 }
+// Whether its tiles go in plane_order, forwards on even and backwards on odd steps,
+// so that a step begins on what the last one left in the Infinity Cache.  Below,
+// the cache holds everything and xcd_order keeps each XCD on the same part of the
+// lattice, whose last lines its L2 still has.  The same ducts, xcd_order /
+// plane_order both ways (forwards only), MB of populations:
+//   FP32    n =  96: 233 MB 53.8 / 59.8 (62.0)   104: 297 MB 108 / 95 (102)   192: 1869 MB 510 / 450 (478)   256: 1122 / 1027 (1054)
+//   FP64    n =  80: 270 MB 66.9 / 78.5 (77.9)    88: 360 MB 123 / 119 (122)
+//   FP16 g  n = 112: 264 MB 92.8 / 91.0 (91.5)   128: 394 MB 126 / 116 (117)  192: 1331 MB 394 / 364 (371)   256:  825 /  755  (766)
+// and the tube of 128^3 nodes, 277 MB, 52.0 / 54.1.
+constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
 
 static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
                            LatticeLayout* L) {
@@ -481,7 +521,9 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 t.lat = lat; t.x0 = x0; t.y0 = y0; t.z0 = z0; t.zn = z1 - z0;
                 L->tiles.push_back(t);
             }
-    xcd_order(L->tiles);
+    L->back = L->fused && fused_bytes(p) > CACHED_BYTES;
+    if (L->back) plane_order(L->tiles);
+    else xcd_order(L->tiles);
     for (size_t k = 0; k < L->tiles.size(); ++k) L->tiles[k].tile_in_lat = (int)k;
     layout_offsets(p, (int64_t)L->tiles.size(), (int64_t)L->ghosts.size(), L);
     return LBM_OK;
@@ -507,6 +549,7 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
         d->hb[0] = base + L.off_h0;
         d->hb[1] = base + L.off_h1;
         d->hbytes = h_buffer_bytes(p);
+        d->back = L.back ? 1 : 0;
     } else {
         d->phi = base + L.off_phi;
         d->gbuf = base + L.off_gbuf;

@@ -21,6 +21,7 @@ struct LatticeLayout {
     int64_t n_fluid = 0, n_ghost = 0, n_solid = 0;
     int64_t n_wall = 0;           // near-wall fluid nodes
     bool fused = false;           // in the fused layout (pflbm.hpp)
+    bool back = false;            // fused: odd steps walk the tile list backwards
     size_t off_desc = 0, off_pop0 = 0, off_pop1 = 0, pop_bytes = 0, off_h0 = 0, off_h1 = 0, h_bytes = 0, off_phi = 0, off_flag = 0,
            off_link = 0, off_tiles = 0, off_partials = 0, off_gbuf = 0, off_ghosts = 0,
            off_wslot = 0, off_hyst = 0, off_wall = 0, off_wgl = 0, off_wrefs = 0, off_wmat = 0,
@@ -45,7 +46,8 @@ int validate_params(const lbm_params* p, const lbm_geometry* geo);
 // Tile width for a lattice of width nx; tile depth for a given tile count target.
 int choose_tx(int nx);
 int choose_tz(const lbm_params* p, int tx, bool fused);
-void xcd_order(std::vector<Tile>& t);   // XCD-aware launch order of a tile list
+void xcd_order(std::vector<Tile>& t);   // XCD-aware launch orders of a tile list
+void plane_order(std::vector<Tile>& t);
 
 // Size of the phase-field lattice (7 or 19).
 inline int phase_q(const lbm_params* p) { return p->q_phase == 19 ? 19 : 7; }
@@ -58,7 +60,7 @@ size_t footprint_bytes(const lbm_params* p);
 
 // Launcher argument qp of a lattice.
 inline int launch_q(const Desc& d) {
-    return (d.q_phase == 19 ? 19 : 7) + (d.hb[0] ? QP_FUSED : 0);
+    return (d.q_phase == 19 ? 19 : 7) + (d.hb[0] ? QP_FUSED : 0) + (d.back ? QP_BACK : 0);
 }
 
 // Full classification + tile table + offsets.  lat: lattice index stamped in

@@ -121,7 +121,8 @@ struct alignas(256) Desc {
     // nodes cut into blocks of tx nodes: direction i of a block is its tx entries
     // from i tx on
     void* hb[2];                   // (NULL: separate passes)
-    int32_t nxh, pad_nxh;          // row length of h, nx padded to the tile width
+    int32_t nxh;                   // row length of h, nx padded to the tile width
+    int32_t back;                  // 1: odd steps walk the tile list backwards
     int64_t hbytes;                // of one buffer
     int64_t step2[2];              // fused layout: the step counter read by the sweep of each
                                    // parity, which writes the other entry for the next step
@@ -172,8 +173,9 @@ constexpr int MODE_READ = 1;   // macroscopic fields / populations to output buf
 constexpr int MODE_INIT = 2;   // equilibria from (phi, u, P) into even-parity slots
 constexpr int MODE_STEP_SV = 3;  // launcher mode: MODE_STEP with sub-voxel walls enabled
 
-// Launcher argument qp: the phase-lattice size, plus QP_FUSED in the fused layout.
-constexpr int QP_FUSED = 256;
+// Launcher argument qp: the phase-lattice size, plus QP_FUSED in the fused layout,
+// plus QP_BACK where odd steps walk the tile list backwards.
+constexpr int QP_FUSED = 256, QP_BACK = 512;
 inline bool is_fused(int qp) { return qp >= QP_FUSED; }
 
 struct GhostRef {              // one pressure ghost: lattice and node

@@ -361,7 +361,7 @@ int rebuild_tables(lbm_server* s) {
     s->phi_groups.clear();
     s->ghost_groups.clear();
     auto lattice_q = [](const Job& j) { return launch_q(j.hdesc); };
-    for (int qp : {QP_FUSED + 7, 7, 19}) {
+    for (int qp : {QP_FUSED + 7, QP_BACK + QP_FUSED + 7, 7, 19}) {
         const int qoff = (int)tiles.size();
         for (int tx : {64, 32, 16}) {
             // lattices with sub-voxel walls run their own instance of the

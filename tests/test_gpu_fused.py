@@ -115,3 +115,21 @@ def test_small_arena_takes_separate_passes():
     for x, y in zip(a.pops(), b.pops()):
         assert _same(x, y)
     b.close()
+
+
+@pytest.mark.parametrize("storage,nx,ny,nz", [("fp32_shift", 130, 131, 133), ("fp16_shift_g", 160, 149, 131),
+                                              ("fp64", 96, 101, 118)])
+def test_tiles_both_ways(storage, nx, ny, nz, monkeypatch):
+    """Lattices beyond the Infinity Cache (more than 285 MB of populations), whose
+    tiles run plane by plane, backwards on odd steps: every tile once a step, and
+    the parts of a plane that do not divide by eight."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    wl = inputs.random_small(nx, ny, nz, seed=34, walls=True, open_x=True, optimised_model=True, u_amp=0.002)
+    a = lbm.Lattice(wl, storage=storage)
+    b = _separate(monkeypatch, lbm, wl, storage)
+    for n in (1, 2, 18):
+        a.step(n)
+        b.step(n)
+        for x, y, what in zip(a.fields(), b.fields(), ("phi", "P", "u")):
+            assert _same(x, y), (storage, a.t, what)
