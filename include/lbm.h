@@ -208,8 +208,8 @@ int lbm_create(const lbm_params *p, const lbm_geometry *geo, const lbm_init *ini
  * the phi pass, the wall pass (wetting values and stencil sums of the
  * near-wall nodes, Sec. II.B), the fused stream-collide sweep (Sec. II.A,
  * Eqs. 1-16), the pressure-face ghosts (Sec. III.A) and the step counter; for
- * lattices in the fused layout (D3Q7 phase lattice, whole-voxel walls, at most
- * 512 MB of populations) all of them are one kernel.  The steps are replayed
+ * lattices in the fused layout (D3Q7 phase lattice, whole-voxel walls) all of
+ * them are one kernel.  The steps are replayed
  * from HIP graphs captured when first needed (one step per AA parity and
  * diagnostic kind, unless a step is one kernel, and 16-step runs without a
  * diagnostic step); while timing is on (lbm_set_timing) every kernel is

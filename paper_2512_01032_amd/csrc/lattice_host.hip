@@ -234,11 +234,47 @@ static void face_planes(const lbm_params* p, LatticeLayout* L) {
     L->gface_count = b;
 }
 
+// Populations (two h buffers and g) from which a fused lattice's tiles go in
+// plane_order, forwards on even and backwards on odd steps, so that a step begins on
+// what the last one left in the Infinity Cache.  Below, the cache holds everything
+// and xcd_order keeps each XCD on the same part of the lattice, whose last lines its
+// L2 still has.  us per step of n x n x 2n ducts, xcd_order / plane_order both ways
+// (forwards only), and their populations:
+//   FP32    n =  96: 233 MB 53.8 / 59.8 (62.0)   104: 297 MB 108 / 95 (102)   192: 1869 MB 510 / 450 (478)   256: 1122 / 1027 (1054)
+//   FP64    n =  80: 270 MB 66.9 / 78.5 (77.9)    88: 360 MB 123 / 119 (122)
+//   FP16 g  n = 112: 264 MB 92.8 / 91.0 (91.5)   128: 394 MB 126 / 116 (117)  192: 1331 MB 394 / 364 (371)   256:  825 /  755  (766)
+// and the tube of 128^3 nodes, 277 MB, 52.0 / 54.1.
+constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
+static int64_t fused_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
+}
+// Tile width in the fused layout: the one with the fewest idle lanes of two or
+// three, the first of equals.  Narrower tiles have the smaller halo (32 x 8 nodes
+// form 244 ring cells, 64 x 4 412), wider ones read whole lines of h and g.  FP64
+// rows of 32 are whole lines already.  Beyond the Infinity Cache rows of 16 in 4 or 2
+// bytes cost more than idle lanes.  Within it 32 and 64 are even (FP32 tube of 128^3
+// nodes 51.8 us at 64, 52.2 at 32; channel 1024 x 48 x 32 43.4, 43.8).  us per step of n x n x 2n ducts at
+// widths 64 / 32 / 16:
+//   FP64    n = 64: 50.4 / 42.5 / 40.8   80: 100 / 76.8 / 65.8   128: 303 / 269 / 284
+//   FP32    n = 64: 22.5 / 20.2 / 20.5   80: 41.1 / 36.4 / 34.8   112: 106 / 108 / 120   176: 379 / 385 / 445   192: 452 / 456 / 517
+//   FP16 g  n = 64: 19.8 / 19.8 / 20.0   80: 38.1 / 34.5 / 32.1   112: 87 / 98 / 90      176: 314 / 330 / 380   192: 365 / 381 / 443
+static int fused_tx(const lbm_params* p) {
+    static const int fp64[3] = {32, 16, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0};
+    const int* c = p->storage == ST_FP64 ? fp64 : (fused_bytes(p) > CACHED_BYTES ? wide : cached);
+    int best = 0, waste_best = 1 << 30;
+    for (int k = 0; k < 3 && c[k]; ++k) {
+        const int waste = (p->nx + c[k] - 1) / c[k] * c[k] - p->nx;
+        if (waste < waste_best) { waste_best = waste; best = c[k]; }
+    }
+    return best;
+}
 // Bytes of one h buffer and of one g group of the fused layout.
 static int64_t h_buffer_bytes(const lbm_params* p) {
     int sh, sg, sphi;
     storage_sizes(p->storage, &sh, &sg, &sphi);
-    const int tx = choose_tx(p->nx);
+    const int tx = fused_tx(p);
     return (int64_t)((p->nx + tx - 1) / tx * tx) * p->ny * p->nz * QH * sh;
 }
 static int64_t g_group_bytes(const lbm_params* p) {
@@ -247,38 +283,20 @@ static int64_t g_group_bytes(const lbm_params* p) {
     return (int64_t)pad_row(p->nx) * p->ny * p->nz * pop_layout(0, sg, sg).pb;
 }
 // Whether a lattice takes the fused layout (one kernel per step): D3Q7 phase
-// lattice, whole-voxel walls, FP64 ones only up to 750 MB of populations (two h
-// buffers and g), and 32-bit offsets.  us per step of an n x n x 2n constricted
-// duct (30 % solid), separate passes / fused:
+// lattice, whole-voxel walls and 32-bit offsets.  us per step of an n x n x 2n
+// constricted duct (30 % solid), separate passes / fused:
 //   FP32    n = 64: 40.2 / 22.7    96: 82.0 / 53.8   128: 151 / 133   192: 555 / 450   256: 1080 / 1027
-//   FP64    n = 64: 61.9 / 49.2    80: 90.3 / 67.1    96: 143 / 137   112: 233 / 209   128:  304 /  302
+//   FP64    n = 64: 61.9 / 42.5    80: 90.3 / 65.8    96: 143 / 137   128: 304 / 269   160: 627 / 536   224: 1676 / 1467
 //   FP16 g  n = 64: 38.6 / 20.2    96: 75.4 / 47.8   128: 125 / 116   192: 416 / 364   256:  781 /  755
 // While the populations stay in the 256 MB Infinity Cache the separate passes are
 // bound by their launches; beyond, by HBM, where the phi pass' second look at h
 // costs more than the second h buffer.
-static int64_t fused_bytes(const lbm_params* p) {
-    int sh, sg, sphi;
-    storage_sizes(p->storage, &sh, &sg, &sphi);
-    return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
-}
 static bool fits_fused(const lbm_params* p) {
     if (phase_q(p) != QH || p->subvoxel) return false;
     if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
-    if (p->storage == ST_FP64 && fused_bytes(p) > (int64_t)750 * 1000 * 1000) return false;
     const int64_t lim = (int64_t)1 << 32;
     return h_buffer_bytes(p) < lim && g_group_bytes(p) < lim;
 }
-// Whether its tiles go in plane_order, forwards on even and backwards on odd steps,
-// so that a step begins on what the last one left in the Infinity Cache.  Below,
-// the cache holds everything and xcd_order keeps each XCD on the same part of the
-// lattice, whose last lines its L2 still has.  The same ducts, xcd_order /
-// plane_order both ways (forwards only), MB of populations:
-//   FP32    n =  96: 233 MB 53.8 / 59.8 (62.0)   104: 297 MB 108 / 95 (102)   192: 1869 MB 510 / 450 (478)   256: 1122 / 1027 (1054)
-//   FP64    n =  80: 270 MB 66.9 / 78.5 (77.9)    88: 360 MB 123 / 119 (122)
-//   FP16 g  n = 112: 264 MB 92.8 / 91.0 (91.5)   128: 394 MB 126 / 116 (117)  192: 1331 MB 394 / 364 (371)   256:  825 /  755  (766)
-// and the tube of 128^3 nodes, 277 MB, 52.0 / 54.1.
-constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
-
 static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
                            LatticeLayout* L) {
     int sh, sg, sphi;
@@ -503,7 +521,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 }
     }
     // tile table: keep tiles holding at least one non-solid node
-    const int tx = choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
+    const int tx = L->fused ? fused_tx(p) : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
     L->tiles.clear();
     for (int z0 = 0; z0 < nz; z0 += tz)
