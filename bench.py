@@ -38,7 +38,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "MLUPS + % HBM roofline, FP32 vs FP16-store at stated error; p99 solve latency"
-SOURCES = ["paper_2512_01032_amd/csrc/kernels_impl.hpp", "paper_2512_01032_amd/csrc/pflbm.hpp"]
+SOURCES = ["paper_2512_01032_amd/csrc/kernels_fused.hpp", "paper_2512_01032_amd/csrc/kernels_impl.hpp",
+           "paper_2512_01032_amd/csrc/pflbm.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic_constricted_duct.json")
 
 
@@ -90,9 +91,9 @@ def _sweep_storage(name):
     """Storage mode of a MODE_STEP sweep dispatch from its kernel name
     (demangled or mangled), else None."""
     import re
-    m = re.search(r"sweep_kernel<(\w+), (\w+), (\w+), 0,", name)
+    m = re.search(r"(?:sweep|step)_kernel<(\w+), (\w+), (\w+), 0,", name)
     if not m:
-        m = re.search(r"sweep_kernelI(f|d)(f|d|DF16_)(f|d|DF16_)Li0E", name)
+        m = re.search(r"(?:sweep|step)_kernelI(f|d)(f|d|DF16_)(f|d|DF16_)Li0E", name)
     if not m:
         return None
     return _STORAGE.get(tuple(_TYPES[t] for t in m.groups()))
@@ -789,7 +790,7 @@ def main():
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(primary["sweep_frac_hbm"], 4),
                      "traffic": traffic,
-                     "kernel": "sweep_kernel (fused stream-collide)",
+                     "kernel": "step_kernel (the whole time step)",
                      "bytes_per_unit": b_alg, "unit_count": "fluid nodes per launch"},
         "cpu_baseline": cpu,
         "streaming_ceiling": dict(streaming, sweep_frac_of_in_place=round(
