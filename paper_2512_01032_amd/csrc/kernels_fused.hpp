@@ -21,7 +21,7 @@
 // second pass over h: FP32 capillary tube 128^3 76.0 -> 52.0 us a step, channel
 // 1024 x 48 x 32 68.1 -> 43.4, FP64 droplet 32^3 16.3 -> 8.1, 2-D channel
 // 25.0 -> 10.7, FP16 g tube 96^3 with hysteresis 48.7 -> 29.6.  Beyond it HBM bounds
-the step (4.5 TB/s, duct 256 x 256 x 512, 1083 -> 1027 with plane_order).  Vector
+// the step (4.5 TB/s, duct 256 x 256 x 512, 1083 -> 1027 with plane_order).  Vector
 // instructions come next (900 to 1050 per wave): the cells' indexes are shifts and
 // masks and the ring rows wave-uniform (with division by the ring length
 // instead 1000 to 1140, tube 55.7 us, FP16 g duct 192 x 192 x 384 483 us against
