@@ -11,10 +11,12 @@
 //
 // Rounding.  The sign term of Eq. 5 and the eps-regularised unit vectors turn a
 // last-bit difference into a visible one within tens of steps, so a lattice
-// must not round differently because it runs fused.  The arithmetic below is
-// written with every rounding explicit (contraction off, fma where one is
-// meant), in the order and with the fused multiply-adds that the separate
-// passes' kernels have; the two layouts agree bitwise.
+// must not round differently because it runs fused.  The arithmetic below and the
+// near-wall functions that both layouts use (wall_normal, wall_sums) have every
+// rounding explicit: contraction off, fma where one is meant.  The separate sweep is
+// compiled with contraction; its node arithmetic is repeated here in the order and
+// with the fused multiply-adds that it has, so the two layouts agree bitwise, which
+// the tests hold for every option.
 //
 // What bounds it.  While the populations stay in the 256 MB Infinity Cache a step
 // was bound by its three to five dependent launches (4 to 9 us each) and by the
@@ -164,9 +166,6 @@ __device__ inline void put_g1(const PA& a, const GNbr<LAY>& nb, uint32_t solid, 
         Store<S>::stx(a, i, off, 0u, v);
     }
 }
-
-__device__ inline double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ inline float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // ------------------------------------------------------- node arithmetic
 // One node's quantities between the stages below (compute precision T).

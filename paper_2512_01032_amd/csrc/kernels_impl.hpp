@@ -582,16 +582,29 @@ __device__ inline void h_eq_pair(int i, const NodeState<T>& s, T href, T& hp, T&
     hm = w * (e - o);
 }
 
-// Unit normal into the fluid from the solid links of a voxel wall.
+__device__ inline double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+// 1 + a / b
+__device__ inline double one_plus_quotient(double a, double b) {
+#pragma clang fp contract(off)
+    return 1.0 + a / b;
+}
+__device__ inline float one_plus_quotient(float a, float b) { return fm(a, __builtin_amdgcn_rcpf(b), 1.0f); }
+
+// Unit normal into the fluid from the solid links of a voxel wall.  This function and
+// wall_sums serve the wall pass and the one-kernel step, so their roundings are
+// written out (contraction off, fma where one is meant) and do not depend on what
+// they are inlined into.
 template <typename T>
 __device__ inline void wall_normal(uint32_t solid, T* nw) {
+#pragma clang fp contract(off)
     nw[0] = nw[1] = nw[2] = T(0);
 #pragma unroll
     for (int i = 1; i < 19; ++i) {
         if (!((solid >> i) & 1u)) continue;
         nw[0] -= T(wg(i) * CX[i]); nw[1] -= T(wg(i) * CY[i]); nw[2] -= T(wg(i) * CZ[i]);
     }
-    const T nn = dev_sqrt(nw[0] * nw[0] + nw[1] * nw[1] + nw[2] * nw[2]);
+    const T nn = dev_sqrt(fm(nw[2], nw[2], fm(nw[1], nw[1], nw[0] * nw[0])));
     const T inn = nn > T(0) ? dev_div(T(1), nn) : T(0);
     nw[0] *= inn; nw[1] *= inn; nw[2] *= inn;
 }
@@ -606,25 +619,26 @@ template <typename T, int MODE, typename PP>
 __device__ inline void wall_sums(uint32_t solid, T pc, const T* nv, const uint32_t* mw, const T* nw,
                                  const T (*s_cs)[16], const PP& pp, int hmode, bool record, T* hist,
                                  int64_t nwl, T* out) {
+#pragma clang fp contract(off)
     const T iTg = T(3);
     T gx = T(0), gy = T(0), gz = T(0), lap = T(0);
     auto pair_sum = [&](int i, T vp, T vm) {
         const T dv = vp - vm;
-        if (CX[i]) gx += T(wg(i) * CX[i]) * dv;
-        if (CY[i]) gy += T(wg(i) * CY[i]) * dv;
-        if (CZ[i]) gz += T(wg(i) * CZ[i]) * dv;
-        lap += T(wg(i)) * ((vp - pc) + (vm - pc));
+        if (CX[i]) gx = fm(T(wg(i) * CX[i]), dv, gx);
+        if (CY[i]) gy = fm(T(wg(i) * CY[i]), dv, gy);
+        if (CZ[i]) gz = fm(T(wg(i) * CZ[i]), dv, gz);
+        lap = fm(T(wg(i)), (vp - pc) + (vm - pc), lap);
     };
 #pragma unroll
     for (int i = 1; i < 19; i += 2)
         pair_sum(i, ((solid >> i) & 1u) ? pc : nv[i], ((solid >> (i + 1)) & 1u) ? pc : nv[i + 1]);
     const T g0[3] = {gx * iTg, gy * iTg, gz * iTg};
-    const T ng = nw[0] * g0[0] + nw[1] * g0[1] + nw[2] * g0[2];
-    T gt[3] = {g0[0] - nw[0] * ng, g0[1] - nw[1] * ng, g0[2] - nw[2] * ng};
-    const T tnn = dev_sqrt(gt[0] * gt[0] + gt[1] * gt[1] + gt[2] * gt[2]);
+    const T ng = fm(nw[2], g0[2], fm(nw[0], g0[0], nw[1] * g0[1]));
+    T gt[3] = {fm(-nw[0], ng, g0[0]), fm(-nw[1], ng, g0[1]), fm(-nw[2], ng, g0[2])};
+    const T tnn = dev_sqrt(fm(gt[2], gt[2], fm(gt[0], gt[0], gt[1] * gt[1])));
     const T itn = dev_div(T(1), tnn + pp[PI_EPS]);
     gt[0] *= itn; gt[1] *= itn; gt[2] *= itn;
-    T a = T(2) * pc - T(1);
+    T a = fm(T(2), pc, T(-1));
     a = a > T(1) - pp[PI_CLAMP_A] ? T(1) - pp[PI_CLAMP_A] : a;
     a = a < -T(1) + pp[PI_CLAMP_A] ? -T(1) + pp[PI_CLAMP_A] : a;
     const T k2W = pp[PI_K2W];
@@ -635,20 +649,24 @@ __device__ inline void wall_sums(uint32_t solid, T pc, const T* nv, const uint32
     auto phis = [&](int i) -> T {
         const int mat = (mw[(i - 1) / 6] >> (4 * ((i - 1) % 6))) & 15u;
         const T ct = s_cs[0][mat], sn = s_cs[1][mat];
-        const T d = -ct * cdot(i, nw[0], nw[1], nw[2]) + sn * cdot(i, gt[0], gt[1], gt[2]);
+        // w . c_i, w = -cos n + sin t: the rounded product is subtracted from the
+        // exact one, the cosine's from the sine's except for the links -x, -y, -z
+        T d;
+        if (i < 7 && i % 2 == 0) d = fm(ct, cdot(i - 1, nw[0], nw[1], nw[2]), -(sn * cdot(i - 1, gt[0], gt[1], gt[2])));
+        else d = fm(sn, cdot(i, gt[0], gt[1], gt[2]), -(ct * cdot(i, nw[0], nw[1], nw[2])));
         // tanh(artanh(a) + 2d/W) by the addition theorem: phi_s,i is exactly
         // phi(x) where d_i = 0 (a link along the normal of a 90-degree wall),
         // so the Laplacian there is exactly zero as in the FP64 model and the
         // sign term of the mobility correction does not flip on rounding noise
         const T t = dev_tanh(k2W * d);
-        T ps = T(0.5) * (T(1) + dev_div(a + t, T(1) + a * t));
+        T ps = T(0.5) * one_plus_quotient(a + t, fm(a, t, T(1)));
         if (hmode) {
             T* hp = hist + (int64_t)(i - 1) * nwl;
             if (record) {
                 *hp = ps;
             } else {
                 const T fresh = ps;
-                ps = pp[PI_HBETA] * *hp + pp[PI_HBETA1] * fresh;
+                ps = fm(pp[PI_HBETA], *hp, pp[PI_HBETA1] * fresh);
                 if (MODE == MODE_STEP) *hp = hmode == 2 ? fresh : ps;
             }
         }
