@@ -21,6 +21,7 @@ struct lbm_handle {
     pflbm::Desc hdesc;           // host copy of the descriptor at creation
     pflbm::Desc* ddesc = nullptr;
     pflbm::Tile* dtiles = nullptr;
+    pflbm::Tile* drtiles = nullptr;   // of the read pass
     int ntiles = 0;
     pflbm::GhostRef* dghosts = nullptr;
     int nghosts = 0;

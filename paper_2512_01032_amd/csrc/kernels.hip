@@ -59,10 +59,9 @@ hipError_t launch_fill_zero(double* p, int64_t n, hipStream_t s) {
 // it takes an agent-scope release per tile, which writes back an XCD's L2: a
 // diagnostic sweep of that duct took 5168 us against 876 us of a plain one.
 constexpr int REDUCE_THREADS = 1024;
-__global__ void __launch_bounds__(REDUCE_THREADS) diag_reduce_kernel(Desc* __restrict__ D) {
+__global__ void __launch_bounds__(REDUCE_THREADS) diag_reduce_kernel(Desc* __restrict__ D, int nt) {
     __shared__ double s_red[REDUCE_THREADS / 64];
     const int j = blockIdx.x, tid = threadIdx.x;
-    const int nt = D->ntiles;
     const double* __restrict__ p = D->partials + (int64_t)j * nt;
     const bool mx = j == P_UMAX;
     auto join = [&](double a, double b) { return mx ? fmax(a, b) : a + b; };
@@ -121,7 +120,7 @@ hipError_t launch_sweep(int storage, int qp, int mode, int tx, int parity, Desc*
         case ST_FP16_G: e = launch_sweep_fp16g(qp, mode, tx, parity, d, tiles, ntiles, diag, ro, in, s); break;
     }
     if (e != hipSuccess || ntiles <= 0 || !diag) return e;
-    diag_reduce_kernel<<<dim3(NPART), dim3(REDUCE_THREADS), 0, s>>>(d);
+    diag_reduce_kernel<<<dim3(NPART), dim3(REDUCE_THREADS), 0, s>>>(d, ntiles);
     return hipGetLastError();
 }
 

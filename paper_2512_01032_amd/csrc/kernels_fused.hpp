@@ -526,6 +526,34 @@ __device__ inline void feed_ghosts(const Desc* D, const GB& gb, const HR& hn, co
     }
 }
 
+// The near-wall threads of a workgroup as a list, one segment per wave (barrier between
+// wall_gather and wall_entry), so that a tile side with one wall node per row costs one
+// wave instead of all.  wall_entry: thread of entry e.
+__device__ inline void wall_gather(uint8_t* list, uint32_t* link, int* cnt, int tid, uint32_t solid) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(solid != 0u);
+    if ((tid & 63) == 0) cnt[tid >> 6] = __builtin_popcountll(m);
+    if (solid) {
+        const int r = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        list[(tid & ~63) + r] = (uint8_t)tid;
+        link[tid] = solid;
+    }
+}
+__device__ inline int wall_total(const int* cnt) {
+    int total = 0;
+#pragma unroll
+    for (int g = 0; g < NTHREADS / 64; ++g) total += cnt[g];
+    return uni(total);
+}
+__device__ inline int wall_entry(const uint8_t* list, const int* cnt, int e) {
+    int g = 0, r = e;
+#pragma unroll
+    for (int j = 0; j < NTHREADS / 64 - 1; ++j) {
+        const int c = cnt[j];
+        if (g == j && r >= c) { r -= c; g = j + 1; }
+    }
+    return list[g * 64 + r];
+}
+
 // One time step of a tile (MODE_STEP), or its read-back (MODE_READ) or
 // initialisation (MODE_INIT).  A tile is TX x (256 / TX) nodes of one z-plane, one
 // per thread.
@@ -688,30 +716,13 @@ step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, bool back,
             if (j < 3 || cidx[j] >= 0) (&s_flag[0][0])[cidx[j]] = (uint8_t)cf[j];
     }
     const bool fluid = active && flag_kind((uint8_t)f) == KIND_FLUID;
-    if (walls) {
-        const uint64_t m = __builtin_amdgcn_ballot_w64(solid != 0u);
-        if ((tid & 63) == 0) s_wcnt[tid >> 6] = __builtin_popcountll(m);
-        if (solid) {
-            const int r = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            s_wlist[(tid & ~63) + r] = (uint8_t)tid;
-            s_wlink[tid] = solid;
-        }
-    }
+    if (walls) wall_gather(s_wlist, s_wlink, s_wcnt, tid, solid);
     lds_barrier();
     if (walls) {
-        int total = 0;
-#pragma unroll
-        for (int g = 0; g < WAVES; ++g) total += s_wcnt[g];
-        total = uni(total);
+        const int total = wall_total(s_wcnt);
         // neighbouring tiles start on different waves (and so SIMDs)
         for (int e = (tid + 64 * tl.tile_in_lat) & (NTHREADS - 1); e < total; e += NTHREADS) {
-            int g = 0, r = e;
-#pragma unroll
-            for (int j = 0; j < WAVES - 1; ++j) {
-                const int c = s_wcnt[j];
-                if (g == j && r >= c) { r -= c; g = j + 1; }
-            }
-            const int id = s_wlist[g * 64 + r];
+            const int id = wall_entry(s_wlist, s_wcnt, e);
             const int wx = id & (TX - 1), wy = id / TX;
             const int cw = (wy + 1) * LW + wx + 1;
             const uint32_t sol = s_wlink[id];
@@ -889,6 +900,44 @@ step_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, bool back,
     }
 }
 
+// Phi of every node [N] into the h buffer of the next step, whose live entries that
+// step writes anyway.
+template <typename T, typename SH>
+__global__ void __launch_bounds__(NTHREADS)
+fused_phi_kernel(const Desc* __restrict__ descs, const Tile* __restrict__ tiles, int par) {
+    const Tile tl = load_tile(tiles);
+    const Desc* D = descs + tl.lat;
+    const int nx = uni(D->nx), ny = uni(D->ny), TX = uni(D->tx), nxh = uni(D->nxh);
+    const int x = tl.x0 + (threadIdx.x & (TX - 1)), y = tl.y0 + threadIdx.x / TX;
+    if (x >= nx || y >= ny) return;
+    const bool linked = uni((int)(D->n_wall > 0 || D->gface_count > 0)) != 0;
+    const uint8_t* __restrict__ flg = unip(D->flag);
+    const SH* __restrict__ h = (const SH*)unip((char*)D->hb[par]);
+    T* __restrict__ out = unip((T*)D->hb[par ^ 1]);
+    const T href = unip(param_block<T>(D))[PI_HREF];
+    for (int k = 0; k < tl.zn; ++k) {
+        const int z = tl.z0 + k, n = x + nx * (y + ny * z);
+        int ox = x, oy = y, oz = z;
+        if (linked) {
+            const uint8_t f = flg[n];
+            if (flag_kind(f) == KIND_SOLID) continue;
+            if (flag_kind(f) == KIND_GHOST) {   // its owner's
+                const int face = flag_sub(f), in = (face & 1) ? -1 : 1;
+                if (face >> 1 == 0) ox += in;
+                else if (face >> 1 == 1) oy += in;
+                else oz += in;
+            }
+        }
+        const SH* const own = h + (int64_t)QH * (nxh * ((int64_t)oy + (int64_t)ny * oz) + ox / TX * TX) + ox % TX;
+        T v[QH], sum = T(0);
+#pragma unroll
+        for (int i = 0; i < QH; ++i) v[i] = (T)own[i * TX];
+#pragma unroll
+        for (int i = 0; i < QH; ++i) sum += v[i];
+        out[n] = href + sum;
+    }
+}
+
 // Populations f_i(x) of a step of parity PAR (canonical [26][N] doubles) into the
 // entries that step reads: h its own, g the AA slots.
 template <typename T, typename SH, typename SG, int PAR>
@@ -939,6 +988,9 @@ hipError_t launch_step_tp(bool back, int mode, Desc* d, const Tile* tiles, int n
             break;
         case MODE_READ:
             step_kernel<T, SH, SG, MODE_READ, true, TX, PAR><<<grid, block, 0, s>>>(d, tiles, back, ro, in);
+            break;
+        case MODE_READ_MARCH:
+            sweep_kernel<T, SH, SG, MODE_READ, true, TX, PAR, QH, false, true><<<grid, block, 0, s>>>(d, tiles, ro, in);
             break;
         case MODE_INIT:
             // (a lattice starts at step 0)

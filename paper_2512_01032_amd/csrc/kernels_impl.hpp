@@ -42,6 +42,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pflbm.hpp"
 
 namespace pflbm {
@@ -682,6 +684,13 @@ __device__ inline void wall_sums(uint32_t solid, T pc, const T* nv, const uint32
     out[0] = gx; out[1] = gy; out[2] = gz; out[3] = lap;
 }
 
+// Near-wall sums of a read pass in the fused layout: by node, after phi [N] in the h
+// buffer of the next step (7 N entries, of which this takes 5 N).
+template <typename T> struct alignas(4 * sizeof(T)) Sums4 { T v[4]; };
+template <typename T> __device__ inline Sums4<T>* read_sums(T* phi, int64_t N) {
+    return (Sums4<T>*)(__attribute__((address_space(1))) Sums4<T>*)(phi + (N + 3) / 4 * 4);
+}
+
 // ---------------------------------------------------------------- wall pass
 // Every near-wall fluid node, after the phi pass (Sec. II.B, Eqs. 17-19): the
 // wall normal into the fluid from the solid links (sub-voxel walls: from the
@@ -697,7 +706,9 @@ __device__ inline void wall_sums(uint32_t solid, T pc, const T* nv, const uint32
 // lattice's list to a multiple of the block size with node -1), so the
 // lattice's constants are block-uniform scalars; all neighbour loads are
 // issued before the arithmetic.
-template <typename T, int MODE>
+// FPAR: -1, or in the fused layout the parity of the step whose read pass follows;
+// phi and the sums are then in the h buffer of the next step, by node.
+template <typename T, int MODE, int FPAR = -1>
 __global__ void __launch_bounds__(NTHREADS)
 wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, int nwalls) {
     __shared__ T s_cs[2][16];   // cos and sin of each material's contact angle
@@ -723,7 +734,7 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
     const int n = wr.node;
     const int64_t sl = wr.slot, nwl = uni(D->n_wall);
     const int x = n % nx, y = (n / nx) % ny, z = n / (nx * ny);
-    const T* __restrict__ phig = unip((const T*)D->phi);
+    const T* __restrict__ phig = unip((const T*)(FPAR < 0 ? D->phi : D->hb[FPAR ^ 1]));
     const uint32_t solid = wr.solid;
     const T* pp = unip(param_block<T>(D));
     const int xs[3] = {x == 0 ? nx - 1 : x - 1, x, x == nx - 1 ? 0 : x + 1};
@@ -753,6 +764,10 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
     const bool record = MODE == MODE_INIT || (MODE == MODE_READ && uni(D->hyst_reset) != 0);
     T sums[4];
     wall_sums<T, MODE>(solid, pc, nv, mw, nw, s_cs, pp, hmode, record, hist, nwl, sums);
+    if constexpr (FPAR >= 0) {
+        read_sums((T*)phig, uni(D->N))[n] = Sums4<T>{{sums[0], sums[1], sums[2], sums[3]}};
+        return;
+    }
     T* __restrict__ out = unip((T*)D->wgl);
     out[sl] = sums[0];
     out[nwl + sl] = sums[1];
@@ -765,8 +780,9 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
 
 // SV: instance with the interpolated bounce-back of sub-voxel walls (step
 // mode only; lattices without sub-voxel walls keep half-way walls in it).
-template <typename T, typename SH, typename SG, int MODE, bool DIAG, int TX, int PAR, int QP, bool SV = false>
-__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(PAR == 1 && sizeof(T) == 4 ? 4 : 1)))
+// FUSED: read pass of a lattice in the fused layout (kernels_fused.hpp).
+template <typename T, typename SH, typename SG, int MODE, bool DIAG, int TX, int PAR, int QP, bool SV = false, bool FUSED = false>
+__global__ void __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : (PAR == 1 ? 4 : (FUSED ? 5 : 1)))))
 sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut ro, InitIn in) {
     // LDS ring of phi and flags: each plane holds the tile plus a one-node
     // halo, LN cells, staged NST cells per thread
@@ -781,7 +797,8 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
 
     const Tile tl = load_tile(tiles);
     Desc* D = descs + tl.lat;
-    const int64_t step = uni(D->step);
+    static_assert(!FUSED || MODE == MODE_READ, "read pass only");
+    const int64_t step = uni(FUSED ? D->step2[PAR] : D->step);
     if (MODE == MODE_STEP && step >= uni(D->stop_step)) return;
     const int64_t time = step - uni(D->t0);
     const int nx = uni(D->nx), ny = uni(D->ny), nz = uni(D->nz);
@@ -796,12 +813,12 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
     const bool diag = DIAG && (MODE == MODE_READ || (dev > 0 && (time % dev) == 0));
     Phys<T> ph;
     ph.load(D);
-    const T* __restrict__ phig = unip((const T*)D->phi);
+    const T* __restrict__ phig = unip((const T*)(FUSED ? D->hb[PAR ^ 1] : D->phi));
     const uint8_t* __restrict__ flg = unip(D->flag);
     const uint32_t* __restrict__ lnk = unip(D->link);
-    typedef Lay<SH, SG, QP> LAYT;
+    typedef typename std::conditional<FUSED, Lay<SG, SG, 0>, Lay<SH, SG, QP>>::type LAYT;
     const auto hb = pop_array<SH, QP, 0, LAYT>(D);
-    const auto gb = pop_array<SG, QG, QP, LAYT>(D);
+    const auto gb = pop_array<SG, QG, FUSED ? 0 : QP, LAYT>(D);
     const int nxp = uni(D->nxp);
     const T Tg = T(TGc);
     const T iTg = T(3), i2Tg2 = T(4.5);
@@ -854,7 +871,7 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
     uint32_t lk_next = 0u;
     int32_t ws_next = 0;
     if (active && (s_flag[1][c0] & LINKED)) lk_next = lnk[x + nx * y + nxy * tl.z0];
-    if (active && (s_flag[1][c0] & F_NEAR_WALL)) ws_next = wsl_arr[x + nx * y + nxy * tl.z0];
+    if (!FUSED && active && (s_flag[1][c0] & F_NEAR_WALL)) ws_next = wsl_arr[x + nx * y + nxy * tl.z0];
     // phi and flags of one plane for the ring, loaded a plane before they
     // are written to LDS
     T nv[NST];
@@ -894,7 +911,7 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
         if (more && active) {
             const uint8_t fn = s_flag[(k + 2) & 3][c0];
             if (fn & LINKED) lk_next = lnk[x + nx * y + nxy * (z + 1)];
-            if (fn & F_NEAR_WALL) ws_next = wsl_arr[x + nx * y + nxy * (z + 1)];
+            if (!FUSED && (fn & F_NEAR_WALL)) ws_next = wsl_arr[x + nx * y + nxy * (z + 1)];
         }
         do {
         if (!active) continue;
@@ -982,14 +999,19 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
         if (solid) {
             // wetting (Eqs. 17-19): the stencil sums with the wall values and
             // the wall normal come from the wall pass
-            const T* __restrict__ wgl = unip((const T*)DC->wgl);
-            gx = wgl[wsl];
-            gy = wgl[wstr + wsl];
-            gz = wgl[2 * wstr + wsl];
-            lap = wgl[3 * wstr + wsl];
-            nw[0] = wgl[4 * wstr + wsl];
-            nw[1] = wgl[5 * wstr + wsl];
-            nw[2] = wgl[6 * wstr + wsl];
+            if constexpr (FUSED) {
+                const Sums4<T> ws = read_sums((T*)phig, N)[(uint32_t)n];
+                gx = ws.v[0]; gy = ws.v[1]; gz = ws.v[2]; lap = ws.v[3];
+            } else {
+                const T* __restrict__ wgl = unip((const T*)DC->wgl);
+                gx = wgl[wsl];
+                gy = wgl[wstr + wsl];
+                gz = wgl[2 * wstr + wsl];
+                lap = wgl[3 * wstr + wsl];
+                nw[0] = wgl[4 * wstr + wsl];
+                nw[1] = wgl[5 * wstr + wsl];
+                nw[2] = wgl[6 * wstr + wsl];
+            }
         }
         st.grad[0] = gx * iTg; st.grad[1] = gy * iTg; st.grad[2] = gz * iTg;
         lap = T(6) * lap;
@@ -1061,7 +1083,13 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
             if (ro.u) { ro.u[n] = (double)st.u[0]; ro.u[N + n] = (double)st.u[1]; ro.u[2 * N + n] = (double)st.u[2]; }
             if (ro.pops) {
                 T dh[QP];
-                read_pops<T, PAR>(hb, nb, solid, ph[PI_INV_SH], dh);
+                if constexpr (FUSED) {
+                    const SH* const own = (const SH*)unip((char*)D->hb[PAR]) +
+                                          (int64_t)QP * (uni(D->nxh) * ((int64_t)y + (int64_t)ny * z) + x / TX * TX) + x % TX;
+                    for (int i = 0; i < QP; ++i) dh[i] = (T)own[i * TX];
+                } else {
+                    read_pops<T, PAR>(hb, nb, solid, ph[PI_INV_SH], dh);
+                }
                 for (int i = 0; i < QP; ++i)
                     ro.pops[(int64_t)i * N + n] = (double)(T(wp<QP>(i)) * ph[PI_HREF] + dh[i]);
             }
@@ -1305,7 +1333,7 @@ sweep_kernel(Desc* __restrict__ descs, const Tile* __restrict__ tiles, ReadOut r
         double v = s_red[tid][0];
         for (int w = 1; w < NTHREADS / 64; ++w)
             v = (tid == P_UMAX) ? fmax(v, s_red[tid][w]) : v + s_red[tid][w];
-        D->partials[(int64_t)tid * uni(D->ntiles) + tl.tile_in_lat] = v;
+        D->partials[(int64_t)tid * (FUSED ? (int)gridDim.x : uni(D->ntiles)) + tl.tile_in_lat] = v;
     }
 }
 
@@ -1436,6 +1464,8 @@ hipError_t launch_wall_compute(int mode, const Desc* d, const WallRef* walls, in
         case MODE_STEP: wall_kernel<T, MODE_STEP><<<grid, block, 0, s>>>(d, walls, nwalls); break;
         case MODE_READ: wall_kernel<T, MODE_READ><<<grid, block, 0, s>>>(d, walls, nwalls); break;
         case MODE_INIT: wall_kernel<T, MODE_INIT><<<grid, block, 0, s>>>(d, walls, nwalls); break;
+        case MODE_READ_MARCH: wall_kernel<T, MODE_READ, 0><<<grid, block, 0, s>>>(d, walls, nwalls); break;
+        case MODE_READ_MARCH + 1: wall_kernel<T, MODE_READ, 1><<<grid, block, 0, s>>>(d, walls, nwalls); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1505,12 +1535,13 @@ hipError_t launch_phi_storage(int qp, int parity, const Desc* d, const Tile* til
                               hipStream_t s, int force) {
     if (ntiles <= 0) return hipSuccess;
     dim3 grid(ntiles), block(NTHREADS);
-    const int key = (qp == 19 ? 2 : 0) + (parity & 1);
+    const int key = (is_fused(qp) ? 4 : (qp == 19 ? 2 : 0)) + (parity & 1);
     switch (key) {
         case 0: phi_kernel<T, SH, SG, 0, QH><<<grid, block, 0, s>>>(d, tiles, force); break;
         case 1: phi_kernel<T, SH, SG, 1, QH><<<grid, block, 0, s>>>(d, tiles, force); break;
         case 2: phi_kernel<T, SH, SG, 0, 19><<<grid, block, 0, s>>>(d, tiles, force); break;
-        default: phi_kernel<T, SH, SG, 1, 19><<<grid, block, 0, s>>>(d, tiles, force); break;
+        case 3: phi_kernel<T, SH, SG, 1, 19><<<grid, block, 0, s>>>(d, tiles, force); break;
+        default: fused_phi_kernel<T, SH><<<grid, block, 0, s>>>(d, tiles, parity & 1); break;
     }
     return hipGetLastError();
 }

@@ -245,6 +245,15 @@ static void face_planes(const lbm_params* p, LatticeLayout* L) {
 //   FP16 g  n = 112: 264 MB 92.8 / 91.0 (91.5)   128: 394 MB 126 / 116 (117)  192: 1331 MB 394 / 364 (371)   256:  825 /  755  (766)
 // and the tube of 128^3 nodes, 277 MB, 52.0 / 54.1.
 constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
+// The same size decides how a lattice in the fused layout is read back: up to it by the
+// one-kernel step's own read instance, beyond by the separate passes' read kernels on
+// tiles of READ_TZ planes, which load every phi once instead of seven populations for
+// three cells.  us of lbm_reduce, one kernel / 4 planes / 8 planes (the same lattice
+// in the separate layout, tiles of 2 or 4 planes):
+//   FP32    duct n = 96: 65 / 75 / 71 (77)     periodic 128^3: 67 / 74 / 73 (84)   duct 160: 197 / 176 / 177 (192)   256: 678 / 544 / 528 (623)
+//   FP64    duct n = 96: 126 / 99 / 100 (101)   160: 417 / 297 / 300 (312)         256: 1443 / 963 / 955 (1058)
+//   FP16 g  periodic 128^3: 64 / 68 / 64 (81)   duct 160: 187 / 162 / 163 (160)    256: 630 / 489 / 453 (480)
+constexpr int READ_TZ = 8;
 static int64_t fused_bytes(const lbm_params* p) {
     int sh, sg, sphi;
     storage_sizes(p->storage, &sh, &sg, &sphi);
@@ -317,7 +326,10 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
         L->off_flag = o; o = align256(o + (size_t)N);
         L->off_link = o; o = align256(o + (size_t)N * 4);
         L->off_tiles = o; o = align256(o + (size_t)ntiles * sizeof(Tile));
+        L->off_rtiles = o; o = align256(o + L->rtiles.size() * sizeof(Tile));
         L->off_partials = o; o = align256(o + (size_t)ntiles * NPART * sizeof(double));
+        L->off_wrefs = o; o = align256(o + L->walls.size() * sizeof(WallRef));
+        L->off_wmat = o; o = align256(o + L->wmat.size() * 4);
         L->off_wslot = o; if (p->hysteresis) o = align256(o + (size_t)N * 4);
         L->off_hyst = o; if (p->hysteresis) o = align256(o + (size_t)(QG - 1) * L->n_wall * sphi);
         L->total = o;
@@ -431,6 +443,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 }
             }
     L->fused = one_kernel;
+    L->back = L->fused && fused_bytes(p) > CACHED_BYTES;
     // solid links of fluid nodes
     for (int z = 0; z < nz; ++z) {
         const int64_t Z[3] = {(int64_t)((z + nz - 1) % nz) * nx * ny, (int64_t)z * nx * ny,
@@ -451,7 +464,8 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
         }
     }
     // slots of the near-wall fluid nodes, in node order (coalesced along x);
-    // the fused layout needs them for the hysteresis table only
+    // the fused layout needs them for the hysteresis table and for a read pass of its
+    // own only
     L->n_wall = 0;
     std::vector<double>().swap(L->wall);
     const bool slots = !L->fused || p->hysteresis;
@@ -459,12 +473,12 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
     L->walls.clear();
     for (int64_t n = 0; n < N; ++n)
         if ((L->link[n] & SOLID_MASK) && flag_kind(L->flag[n]) == KIND_FLUID) {
-            if (!L->fused) L->walls.push_back(WallRef{0, (int32_t)n, (int32_t)L->n_wall, L->link[n] & SOLID_MASK});
+            if (!L->fused || L->back) L->walls.push_back(WallRef{0, (int32_t)n, (int32_t)L->n_wall, L->link[n] & SOLID_MASK});
             if (slots) L->wslot[n] = (int32_t)L->n_wall;
             ++L->n_wall;
         }
     // materials of the solid links, packed per slot
-    L->wmat.assign(L->fused ? 0 : (size_t)3 * L->n_wall, 0u);
+    L->wmat.assign((size_t)3 * L->walls.size(), 0u);
     for (const WallRef& w : L->walls) {
         const int64_t n = w.node;
         const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((int64_t)nx * ny));
@@ -523,26 +537,34 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
     // tile table: keep tiles holding at least one non-solid node
     const int tx = L->fused ? fused_tx(p) : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
-    L->tiles.clear();
-    for (int z0 = 0; z0 < nz; z0 += tz)
-        for (int y0 = 0; y0 < ny; y0 += ty)
-            for (int x0 = 0; x0 < nx; x0 += tx) {
-                bool any = false;
-                const int z1 = std::min(nz, z0 + tz), y1 = std::min(ny, y0 + ty), x1 = std::min(nx, x0 + tx);
-                for (int z = z0; z < z1 && !any; ++z)
-                    for (int y = y0; y < y1 && !any; ++y)
-                        for (int x = x0; x < x1; ++x)
-                            if (flag_kind(L->flag[x + (int64_t)nx * (y + (int64_t)ny * z)]) != KIND_SOLID) { any = true; break; }
-                if (!any) continue;
-                Tile t;
-                memset(&t, 0, sizeof(t));
-                t.lat = lat; t.x0 = x0; t.y0 = y0; t.z0 = z0; t.zn = z1 - z0;
-                L->tiles.push_back(t);
-            }
-    L->back = L->fused && fused_bytes(p) > CACHED_BYTES;
+    auto list_tiles = [&](int tz, std::vector<Tile>* tiles) {
+        tiles->clear();
+        for (int z0 = 0; z0 < nz; z0 += tz)
+            for (int y0 = 0; y0 < ny; y0 += ty)
+                for (int x0 = 0; x0 < nx; x0 += tx) {
+                    bool any = false;
+                    const int z1 = std::min(nz, z0 + tz), y1 = std::min(ny, y0 + ty), x1 = std::min(nx, x0 + tx);
+                    for (int z = z0; z < z1 && !any; ++z)
+                        for (int y = y0; y < y1 && !any; ++y)
+                            for (int x = x0; x < x1; ++x)
+                                if (flag_kind(L->flag[x + (int64_t)nx * (y + (int64_t)ny * z)]) != KIND_SOLID) { any = true; break; }
+                    if (!any) continue;
+                    Tile t;
+                    memset(&t, 0, sizeof(t));
+                    t.lat = lat; t.x0 = x0; t.y0 = y0; t.z0 = z0; t.zn = z1 - z0;
+                    tiles->push_back(t);
+                }
+    };
+    list_tiles(tz, &L->tiles);
     if (L->back) plane_order(L->tiles);
     else xcd_order(L->tiles);
-    for (size_t k = 0; k < L->tiles.size(); ++k) L->tiles[k].tile_in_lat = (int)k;
+    L->rtiles.clear();
+    if (L->back) {
+        list_tiles(std::min(READ_TZ, nz), &L->rtiles);
+        xcd_order(L->rtiles);
+    }
+    for (std::vector<Tile>* v : {&L->tiles, &L->rtiles})
+        for (size_t k = 0; k < v->size(); ++k) (*v)[k].tile_in_lat = (int)k;
     layout_offsets(p, (int64_t)L->tiles.size(), (int64_t)L->ghosts.size(), L);
     return LBM_OK;
 }
@@ -568,12 +590,13 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
         d->hb[1] = base + L.off_h1;
         d->hbytes = h_buffer_bytes(p);
         d->back = L.back ? 1 : 0;
+        d->march = L.rtiles.empty() ? 0 : 1;
     } else {
         d->phi = base + L.off_phi;
         d->gbuf = base + L.off_gbuf;
         d->wgl = base + L.off_wgl;
-        d->wmat = (const uint32_t*)(base + L.off_wmat);
     }
+    d->wmat = (const uint32_t*)(base + L.off_wmat);
     d->q_phase = phase_q(p);
     d->hysteresis = p->hysteresis;
     d->hyst_reset = 0;
@@ -710,6 +733,8 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     }
     HIPCHK(hipMemcpyAsync(base + L.off_tiles, L.tiles.data(), L.tiles.size() * sizeof(Tile),
                           hipMemcpyHostToDevice, s));
+    if (!L.rtiles.empty())
+        HIPCHK(hipMemcpyAsync(base + L.off_rtiles, L.rtiles.data(), L.rtiles.size() * sizeof(Tile), hipMemcpyHostToDevice, s));
     if (!L.fused && !L.ghosts.empty())
         HIPCHK(hipMemcpyAsync(base + L.off_ghosts, L.ghosts.data(), L.ghosts.size() * sizeof(GhostRef),
                               hipMemcpyHostToDevice, s));
@@ -738,7 +763,7 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
             const int32_t on = 1, off = 0;
             HIPCHK(hipMemcpyAsync(&ddesc->hyst_reset, &on, sizeof(on), hipMemcpyHostToDevice, s));
             HIPCHK(hipStreamSynchronize(s));
-            int rc = read_lattice(p->storage, *hdesc, (int)(step0 & 1), ddesc, dtiles, nt,
+            int rc = read_lattice(p->storage, *hdesc, (int)(step0 & 1), ddesc, (const Tile*)(base + L.read_tiles_at()), L.n_read_tiles(),
                                   (const WallRef*)(base + L.off_wrefs), (int)L.walls.size(), 0, nullptr,
                                   nullptr, nullptr, nullptr, s);
             HIPCHK(hipMemcpyAsync(&ddesc->hyst_reset, &off, sizeof(off), hipMemcpyHostToDevice, s));
@@ -780,8 +805,8 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     }
     ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
     InitIn in = {du, dP, dphi};
-    hipError_t e = launch_wall(p->storage, MODE_INIT, ddesc, (const WallRef*)(base + L.off_wrefs),
-                               (int)L.walls.size(), s);
+    hipError_t e = L.fused ? hipSuccess : launch_wall(p->storage, MODE_INIT, ddesc, (const WallRef*)(base + L.off_wrefs),
+                                                      (int)L.walls.size(), s);
     if (e == hipSuccess) e = launch_sweep(p->storage, lq, MODE_INIT, L.tx, 0, ddesc, dtiles, nt, 0, ro, in, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (du) hipFree(du);
@@ -919,9 +944,10 @@ int read_lattice_staged(int storage, const Desc& hdesc, int parity, Desc* d_desc
     // nodes of dropped (all-solid) tiles are written by no read kernel: they
     // read 0 from the cleared staging
     hipError_t e = launch_fill_zero(buf, (int64_t)nd, s);
-    if (e == hipSuccess && !is_fused(lq)) e = launch_phi(storage, qh, parity, d_desc, d_tiles, ntiles, s, 1);
-    if (e == hipSuccess && !is_fused(lq)) e = launch_wall(storage, MODE_READ, d_desc, d_walls, nwalls, s);
-    if (e == hipSuccess) e = launch_sweep(storage, lq, MODE_READ, hdesc.tx, parity, d_desc, d_tiles, ntiles, 1, ro, in, s);
+    if (e == hipSuccess && (!is_fused(lq) || hdesc.march)) e = launch_phi(storage, lq, parity, d_desc, d_tiles, ntiles, s, 1);
+    if (e == hipSuccess && (!is_fused(lq) || hdesc.march))
+        e = launch_wall(storage, hdesc.march ? MODE_READ_MARCH + (parity & 1) : MODE_READ, d_desc, d_walls, nwalls, s);
+    if (e == hipSuccess) e = launch_sweep(storage, lq, hdesc.march ? MODE_READ_MARCH : MODE_READ, hdesc.tx, parity, d_desc, d_tiles, ntiles, 1, ro, in, s);
     CopyOut c[8];
     int nc = 0;
     auto add = [&](double* dst, const double* src, size_t rows) {

@@ -21,8 +21,12 @@ struct LatticeLayout {
     int64_t n_fluid = 0, n_ghost = 0, n_solid = 0;
     int64_t n_wall = 0;           // near-wall fluid nodes
     bool fused = false;           // in the fused layout (pflbm.hpp)
-    bool back = false;            // fused: odd steps walk the tile list backwards
-    size_t off_desc = 0, off_pop0 = 0, off_pop1 = 0, pop_bytes = 0, off_h0 = 0, off_h1 = 0, h_bytes = 0, off_phi = 0, off_flag = 0,
+    bool back = false;            // fused, beyond the Infinity Cache: odd steps walk the tile list
+                                  // backwards, and the read pass has kernels and tiles of its own
+    std::vector<Tile> rtiles;     // these tiles
+    size_t read_tiles_at() const { return rtiles.empty() ? off_tiles : off_rtiles; }
+    int n_read_tiles() const { return (int)(rtiles.empty() ? tiles.size() : rtiles.size()); }
+    size_t off_rtiles = 0, off_desc = 0, off_pop0 = 0, off_pop1 = 0, pop_bytes = 0, off_h0 = 0, off_h1 = 0, h_bytes = 0, off_phi = 0, off_flag = 0,
            off_link = 0, off_tiles = 0, off_partials = 0, off_gbuf = 0, off_ghosts = 0,
            off_wslot = 0, off_hyst = 0, off_wall = 0, off_wgl = 0, off_wrefs = 0, off_wmat = 0,
            total = 0;

@@ -101,6 +101,7 @@ extern "C" int lbm_create(const lbm_params* p, const lbm_geometry* geo, const lb
     h->ddesc = (Desc*)(h->base + h->L.off_desc);
     h->dtiles = (Tile*)(h->base + h->L.off_tiles);
     h->ntiles = (int)h->L.tiles.size();
+    h->drtiles = (Tile*)(h->base + h->L.read_tiles_at());
     h->dghosts = (GhostRef*)(h->base + h->L.off_ghosts);
     h->nghosts = (int)h->L.ghosts.size();
     h->dwalls = (WallRef*)(h->base + h->L.off_wrefs);
@@ -167,7 +168,7 @@ static int enqueue_steps(lbm_handle* h, int64_t t0, int64_t n, hipStream_t s, bo
         }
         const int par = (int)(t & 1);
         if (!fused) HIPRET(launch_phi(storage, qp, par, h->ddesc, h->dtiles, h->ntiles, s));
-        if (h->nwalls) HIPRET(launch_wall(storage, MODE_STEP, h->ddesc, h->dwalls, h->nwalls, s));
+        if (!fused && h->nwalls) HIPRET(launch_wall(storage, MODE_STEP, h->ddesc, h->dwalls, h->nwalls, s));
         if (events) HIPRET(hipEventRecord(e1, s));
         HIPRET(launch_sweep(storage, qp, h->p.subvoxel ? MODE_STEP_SV : MODE_STEP, h->L.tx, par, h->ddesc,
                             h->dtiles, h->ntiles, diag, ro, in, s));
@@ -278,15 +279,15 @@ extern "C" int lbm_read_fields(lbm_handle* h, uint32_t mask, double* phi, double
     if (!h) { set_error("handle is NULL"); return LBM_E_INVAL; }
     HIPRET(hipSetDevice(h->device));
     HIPRET(hipStreamSynchronize(h->stream));
-    return read_lattice(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->dtiles, h->ntiles,
+    return read_lattice(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->drtiles, h->L.n_read_tiles(),
                         h->dwalls, h->nwalls, mask, phi, P, u, pops, h->stream);
 }
 
 extern "C" int lbm_reduce(lbm_handle* h, lbm_diag* d) {
     if (!h || !d) { set_error("NULL argument"); return LBM_E_INVAL; }
     HIPRET(hipSetDevice(h->device));
-    int rc = read_lattice(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->dtiles,
-                          h->ntiles, h->dwalls, h->nwalls, 0, nullptr, nullptr, nullptr, nullptr, h->stream);
+    int rc = read_lattice(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->drtiles,
+                          h->L.n_read_tiles(), h->dwalls, h->nwalls, 0, nullptr, nullptr, nullptr, nullptr, h->stream);
     if (rc != LBM_OK) return rc;
     double v[NPART];
     HIPRET(hipMemcpy(v, h->ddesc->diag, sizeof(v), hipMemcpyDeviceToHost));

@@ -153,7 +153,7 @@ struct alignas(256) Desc {
     // outputs of the last diagnostic reduction
     double diag[NPART];
     int32_t unstable;              // sticky: NaN or |u| > u_max seen
-    int32_t pad1;
+    int32_t march;                 // fused layout: the read pass has kernels and tiles of its own
 };
 
 enum ParamIndex {
@@ -172,6 +172,9 @@ constexpr int MODE_STEP = 0;   // stream + collide, AA in place
 constexpr int MODE_READ = 1;   // macroscopic fields / populations to output buffers
 constexpr int MODE_INIT = 2;   // equilibria from (phi, u, P) into even-parity slots
 constexpr int MODE_STEP_SV = 3;  // launcher mode: MODE_STEP with sub-voxel walls enabled
+
+constexpr int MODE_READ_MARCH = 4;  // launcher mode: read pass by the separate passes' kernels in the
+                                    // fused layout (launch_wall: plus the parity)
 
 // Launcher argument qp: the phase-lattice size, plus QP_FUSED in the fused layout,
 // plus QP_BACK where odd steps walk the tile list backwards.
@@ -216,7 +219,8 @@ struct InitIn {                // device inputs of MODE_INIT
 // every lattice in the table; parity: AA parity of the step every lattice
 // in the table is at; tx: tile width of every tile (16, 32 or 64).  In
 // the fused layout the sweep is the whole step, and no other launch goes with
-// it.
+// it; before a sweep in MODE_READ_MARCH, launch_phi and launch_wall with that mode put
+// phi and the near-wall sums into the h buffer of the next step.
 // force: run the phi pass even for lattices past their stop step (read-back).
 hipError_t launch_phi(int storage, int qp, int parity, const Desc* d, const Tile* tiles, int ntiles,
                       hipStream_t s, int force = 0);

@@ -62,6 +62,6 @@ extern "C" int lbm_read_fields_noalloc(lbm_handle* h, uint32_t mask, double* phi
     if (rc != LBM_OK) return rc;
     e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) { set_error("hipStreamSynchronize: %s", hipGetErrorString(e)); return LBM_E_DEVICE; }
-    return read_lattice_staged(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->dtiles,
-                               h->ntiles, h->dwalls, h->nwalls, mask, phi, P, u, pops, buf, nullptr, h->stream);
+    return read_lattice_staged(h->p.storage, h->hdesc, (int)(h->step & 1), h->ddesc, h->drtiles,
+                               h->L.n_read_tiles(), h->dwalls, h->nwalls, mask, phi, P, u, pops, buf, nullptr, h->stream);
 }

@@ -293,10 +293,10 @@ int read_back(lbm_server* s) {
                 s->hpin = nullptr;
             }
             Desc* dd = s->dtable + job->slot;
-            const Tile* dt = (const Tile*)(s->arena + job->off + job->L.off_tiles);
+            const Tile* dt = (const Tile*)(s->arena + job->off + job->L.read_tiles_at());
             const WallRef* dw = (const WallRef*)(s->arena + job->off + job->L.off_wrefs);
             rc = read_lattice_staged(s->cfg.storage, job->hdesc, (int)(job->nsteps & 1), dd, dt,
-                                     (int)job->L.tiles.size(), dw, (int)job->L.walls.size(), mask, job->phi,
+                                     job->L.n_read_tiles(), dw, (int)job->L.walls.size(), mask, job->phi,
                                      job->P, job->u, nullptr, s->dstage, s->hpin, s->up_stream);
             double v[NPART];
             if (rc == LBM_OK) {
@@ -386,12 +386,12 @@ int rebuild_tables(lbm_server* s) {
             s->ghost_groups.push_back({qp, 0, goff, (int)ghosts.size() - goff});
     }
     for (auto& j : s->active) {
+        if (j->L.fused) continue;   // (its step kernel does the near-wall nodes and the step counter)
         for (WallRef w : j->L.walls) { w.lat = j->slot; walls.push_back(w); }
         // the wall pass takes its lattice constants per block: pad each
         // lattice's list to whole blocks (node -1 is skipped)
         while (walls.size() % NTHREADS) walls.push_back(WallRef{j->slot, -1, 0, 0u});
-        // (the step kernel advances its lattices' step counters)
-        if (!j->L.fused) s->hslots.push_back(j->slot);
+        s->hslots.push_back(j->slot);
     }
     s->nmirror = 0;
     for (auto& j : s->active) s->nmirror = std::max(s->nmirror, j->slot + 1);
