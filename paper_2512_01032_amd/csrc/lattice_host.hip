@@ -269,9 +269,13 @@ static int64_t fused_bytes(const lbm_params* p) {
 //   FP64    n = 64: 50.4 / 42.5 / 40.8   80: 100 / 76.8 / 65.8   128: 303 / 269 / 284
 //   FP32    n = 64: 22.5 / 20.2 / 20.5   80: 41.1 / 36.4 / 34.8   112: 106 / 108 / 120   176: 379 / 385 / 445   192: 452 / 456 / 517
 //   FP16 g  n = 64: 19.8 / 19.8 / 20.0   80: 38.1 / 34.5 / 32.1   112: 87 / 98 / 90      176: 314 / 330 / 380   192: 365 / 381 / 443
+// With contact-angle hysteresis a tile waits for the history of its near-wall nodes, and
+// beyond the cache fewer tiles of 32 than of 64 have any (FP32 ducts n = 128: 162 at 64,
+// 153 at 32; 192: 509, 502; channel 1024 x 64 x 64: 195, 218, against 228 in the
+// separate layout).
 static int fused_tx(const lbm_params* p) {
-    static const int fp64[3] = {32, 16, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0};
-    const int* c = p->storage == ST_FP64 ? fp64 : (fused_bytes(p) > CACHED_BYTES ? wide : cached);
+    static const int fp64[3] = {32, 16, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
+    const int* c = p->storage == ST_FP64 ? fp64 : (fused_bytes(p) <= CACHED_BYTES ? cached : (p->hysteresis ? hyst : wide));
     int best = 0, waste_best = 1 << 30;
     for (int k = 0; k < 3 && c[k]; ++k) {
         const int waste = (p->nx + c[k] - 1) / c[k] * c[k] - p->nx;
@@ -300,8 +304,20 @@ static int64_t g_group_bytes(const lbm_params* p) {
 // While the populations stay in the 256 MB Infinity Cache the separate passes are
 // bound by their launches; beyond, by HBM, where the phi pass' second look at h
 // costs more than the second h buffer.
+// With hysteresis a near-wall node reads and writes up to 18 history entries one after
+// another, which a tile of the one-kernel step waits for and the wall pass hides behind
+// the others: beyond the cache that costs more than the passes do, but for FP32 lattices
+// of up to 3 GB.  us per step of ducts with hysteresis, separate passes / fused:
+//   FP32    n = 96: 86 / 60   128: 159 / 153   160: 309 / 292   192: 563 / 502   224: 915 / 816   256: 1103 / 1125
+//   FP64    n = 48: 52 / 36    96: 149 / 161   128: 311 / 328   160: 635 / 616   192: 964 / 1022  256: 2176 / 2333
+//   FP16 g  n = 96: 79 / 51   112: 119 / 111   128: 130 / 144   160: 260 / 260   192: 423 / 431   256: 801 / 936
+constexpr int64_t HYST_FP32_BYTES = (int64_t)3 * 1000 * 1000 * 1000;
 static bool fits_fused(const lbm_params* p) {
     if (phase_q(p) != QH || p->subvoxel) return false;
+    if (p->hysteresis && fused_bytes(p) > CACHED_BYTES) {
+        const bool fp32 = p->storage == ST_FP32 || p->storage == ST_FP32_SHIFT;
+        if (!fp32 || fused_bytes(p) > HYST_FP32_BYTES) return false;
+    }
     if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
     const int64_t lim = (int64_t)1 << 32;
     return h_buffer_bytes(p) < lim && g_group_bytes(p) < lim;
