@@ -260,7 +260,10 @@ static int64_t fused_bytes(const lbm_params* p) {
     return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
 }
 // Tile width in the fused layout: the one with the fewest idle lanes of two or
-// three, the first of equals.  Narrower tiles have the smaller halo (32 x 8 nodes
+// three, in rows and columns; of equals the one with the fewest in a row, then the
+// first.  A flat lattice leaves most rows of a narrow tile idle: FP64 1024 x 1 x 1024
+// took 231 us a step at 32 (8 rows), 150 at 64 (4 rows), 162 in the separate layout;
+// FP32 130 x 6 x 600 30 at 16, 24 at 32.  Narrower tiles have the smaller halo (32 x 8 nodes
 // form 244 ring cells, 64 x 4 412), wider ones read whole lines of h and g.  FP64
 // rows of 32 are whole lines already.  Beyond the Infinity Cache rows of 16 in 4 or 2
 // bytes cost more than idle lanes.  Within it 32 and 64 are even (FP32 tube of 128^3
@@ -274,12 +277,18 @@ static int64_t fused_bytes(const lbm_params* p) {
 // 153 at 32; 192: 509, 502; channel 1024 x 64 x 64: 195, 218, against 228 in the
 // separate layout).
 static int fused_tx(const lbm_params* p) {
-    static const int fp64[3] = {32, 16, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
+    static const int fp64[3] = {32, 16, 64}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
     const int* c = p->storage == ST_FP64 ? fp64 : (fused_bytes(p) <= CACHED_BYTES ? cached : (p->hysteresis ? hyst : wide));
-    int best = 0, waste_best = 1 << 30;
+    int best = 0;
+    int64_t lanes_best = 0, row_best = 0;
     for (int k = 0; k < 3 && c[k]; ++k) {
-        const int waste = (p->nx + c[k] - 1) / c[k] * c[k] - p->nx;
-        if (waste < waste_best) { waste_best = waste; best = c[k]; }
+        const int tx = c[k], ty = NTHREADS / tx;
+        const int64_t row = (p->nx + tx - 1) / tx * tx, lanes = row * ((p->ny + ty - 1) / ty * ty);
+        if (!best || lanes < lanes_best || (lanes == lanes_best && row < row_best)) {
+            best = tx;
+            lanes_best = lanes;
+            row_best = row;
+        }
     }
     return best;
 }

@@ -41,3 +41,26 @@ def test_hysteresis_layout(shape, storage, fused, monkeypatch):
     a = lbm.Lattice(wl, storage=storage)
     b = separate(monkeypatch, wl, storage)
     assert is_fused(a, b) == fused
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32_shift"])
+@pytest.mark.parametrize("shape,tiles", [
+    ((64, 1, 40), 40),       # one row: tiles of 64 x 4, not of 32 x 8
+    ((130, 6, 20), 100),     # 160 x 8 lanes in tiles of 32 x 8, 144 x 16 in narrower ones
+    ((2, 2, 50), 50),        # equal lanes at every width: the narrowest
+    ((96, 16, 10), 60),      # 3 x 2 tiles of 32 x 8
+])
+def test_idle_rows_count(shape, tiles, storage, monkeypatch):
+    """Tiles of flat lattices leave few rows idle, and step like the separate passes."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    wl = inputs.random_small(*shape, seed=9, u_amp=2e-4, optimised_model=True)
+    a = lbm.Lattice(wl, storage=storage)
+    b = separate(monkeypatch, wl, storage)
+    assert a.info()["n_tiles"] == tiles
+    for n in (1, 4):
+        a.step(n)
+        b.step(n)
+        for x, y in zip(a.fields() + a.pops(), b.fields() + b.pops()):
+            assert np.isfinite(y).all()
+            assert np.array_equal(x, y)
