@@ -234,18 +234,43 @@ static void face_planes(const lbm_params* p, LatticeLayout* L) {
     L->gface_count = b;
 }
 
-// Populations (two h buffers and g) from which a fused lattice's tiles go in
-// plane_order, forwards on even and backwards on odd steps, so that a step begins on
-// what the last one left in the Infinity Cache.  Below, the cache holds everything
-// and xcd_order keeps each XCD on the same part of the lattice, whose last lines its
-// L2 still has.  us per step of n x n x 2n ducts, xcd_order / plane_order both ways
-// (forwards only), and their populations:
-//   FP32    n =  96: 233 MB 53.8 / 59.8 (62.0)   104: 297 MB 108 / 95 (102)   192: 1869 MB 510 / 450 (478)   256: 1122 / 1027 (1054)
-//   FP64    n =  80: 270 MB 66.9 / 78.5 (77.9)    88: 360 MB 123 / 119 (122)
-//   FP16 g  n = 112: 264 MB 92.8 / 91.0 (91.5)   128: 394 MB 126 / 116 (117)  192: 1331 MB 394 / 364 (371)   256:  825 /  755  (766)
-// and the tube of 128^3 nodes, 277 MB, 52.0 / 54.1.
-constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
-// The same size decides how a lattice in the fused layout is read back: up to it by the
+// Populations of the fused layout (two h buffers and g) in bytes, and in the cache lines
+// that a full row of nodes touches: a row of g begins a block of 64 nodes, where every
+// direction begins a line, and a row of h comes in blocks of at least 16 nodes.
+static int64_t fused_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
+}
+static int64_t fused_line_bytes(const lbm_params* p) {
+    int sh, sg, sphi;
+    storage_sizes(p->storage, &sh, &sg, &sphi);
+    const int64_t h = (int64_t)(p->nx + 15) / 16 * 16 * 2 * QH * sh;
+    const int64_t g = ((int64_t)p->nx / 64 * 64 * sg + (p->nx % 64 * sg + 127) / 128 * 128) * QG;
+    return (h + g) * p->ny * p->nz;
+}
+// Whether a lattice goes beyond the 256 MB Infinity Cache: by its populations, or by the
+// lines of the blocks of 32 nodes that are not all solid (used, of all).  Beyond it the
+// tiles go in plane_order, forwards on even and backwards on odd steps, so that a step
+// begins on what the last one left in the cache.  Below, the cache holds everything and
+// xcd_order keeps each XCD on the same part of the lattice, whose last lines its L2
+// still has.  us per step, xcd_order / plane_order both ways, populations and lines:
+//   n x n x 2n ducts
+//   FP32    n =  96: 233, 157 MB 51.8 / 58.2    104: 297, 228 MB 108 / 95    192: 1869 MB 510 / 450   256: 1122 / 1027
+//   FP64    n =  80: 270, 180 MB 66.9 / 78.5     88: 360 MB 123 / 119
+//   FP16 g  n = 112: 264, 188 MB 92.8 / 91.0    128: 394 MB 126 / 116       192: 1331 MB 394 / 364   256:  825 /  755
+//   periodic cubes and others
+//   FP32    120^3: 228, 243 MB 58.1 / 61.7   128^3: 277, 277 MB 91.5 / 73.4   17 x 256 x 256: 147, 277 MB 103 / 95   33 x 200 x 300: 261, 453 MB 188 / 144
+//   FP64     96^3: 234, 234 MB 66.7 / 68.5   1024 x 1 x 1024: 277, 277 MB 150 / 140   1 x 500 x 500: 66, 1056 MB 379 / 333
+//   FP16 g  128^3: 197, 197 MB 48.2 / 49.6   136^3: 236, 281 MB 133 / 107      33 x 200 x 300: 186, 307 MB 160 / 131
+// The separate passes, which all of these took before, need 90.6 us for the FP32 cube of
+// 128, 97 for 17 x 256 x 256 and 139 for FP16 g 33 x 200 x 300.
+constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000, CACHED_LINE_BYTES = (int64_t)250 * 1000 * 1000;
+static bool beyond_cache(const lbm_params* p, int64_t used, int64_t of) {
+    return fused_bytes(p) > CACHED_BYTES ||
+           (double)fused_line_bytes(p) * ((double)used / (double)of) > (double)CACHED_LINE_BYTES;
+}
+// The same line decides how a lattice in the fused layout is read back: up to it by the
 // one-kernel step's own read instance, beyond by the separate passes' read kernels on
 // tiles of READ_TZ planes, which load every phi once instead of seven populations for
 // three cells.  us of lbm_reduce, one kernel / 4 planes / 8 planes (the same lattice
@@ -254,11 +279,6 @@ constexpr int64_t CACHED_BYTES = (int64_t)285 * 1000 * 1000;
 //   FP64    duct n = 96: 126 / 99 / 100 (101)   160: 417 / 297 / 300 (312)         256: 1443 / 963 / 955 (1058)
 //   FP16 g  periodic 128^3: 64 / 68 / 64 (81)   duct 160: 187 / 162 / 163 (160)    256: 630 / 489 / 453 (480)
 constexpr int READ_TZ = 8;
-static int64_t fused_bytes(const lbm_params* p) {
-    int sh, sg, sphi;
-    storage_sizes(p->storage, &sh, &sg, &sphi);
-    return (int64_t)p->nx * p->ny * p->nz * (2 * QH * sh + QG * sg);
-}
 // Tile width in the fused layout: the one with the fewest idle lanes of two or
 // three, in rows and columns; of equals the one with the fewest in a row, then the
 // first.  A flat lattice leaves most rows of a narrow tile idle: FP64 1024 x 1 x 1024
@@ -266,7 +286,8 @@ static int64_t fused_bytes(const lbm_params* p) {
 // FP32 130 x 6 x 600 30 at 16, 24 at 32.  Narrower tiles have the smaller halo (32 x 8 nodes
 // form 244 ring cells, 64 x 4 412), wider ones read whole lines of h and g.  FP64
 // rows of 32 are whole lines already.  Beyond the Infinity Cache rows of 16 in 4 or 2
-// bytes cost more than idle lanes.  Within it 32 and 64 are even (FP32 tube of 128^3
+// bytes cost more than idle lanes, and of FP64 too (cubes of 104 nodes 108 us at 32,
+// 117 at 16, 113.5 in the separate layout; 120: 145, 167; 200: 762, 807).  Within it 32 and 64 are even (FP32 tube of 128^3
 // nodes 51.8 us at 64, 52.2 at 32; channel 1024 x 48 x 32 43.4, 43.8).  us per step of n x n x 2n ducts at
 // widths 64 / 32 / 16:
 //   FP64    n = 64: 50.4 / 42.5 / 40.8   80: 100 / 76.8 / 65.8   128: 303 / 269 / 284
@@ -276,9 +297,9 @@ static int64_t fused_bytes(const lbm_params* p) {
 // beyond the cache fewer tiles of 32 than of 64 have any (FP32 ducts n = 128: 162 at 64,
 // 153 at 32; 192: 509, 502; channel 1024 x 64 x 64: 195, 218, against 228 in the
 // separate layout).
-static int fused_tx(const lbm_params* p) {
-    static const int fp64[3] = {32, 16, 64}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
-    const int* c = p->storage == ST_FP64 ? fp64 : (fused_bytes(p) <= CACHED_BYTES ? cached : (p->hysteresis ? hyst : wide));
+static int fused_tx(const lbm_params* p, bool beyond) {
+    static const int fp64[3] = {32, 16, 64}, fp64_wide[3] = {32, 64, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
+    const int* c = p->storage == ST_FP64 ? (beyond && p->nx > 16 ? fp64_wide : fp64) : (!beyond ? cached : (p->hysteresis ? hyst : wide));
     int best = 0;
     int64_t lanes_best = 0, row_best = 0;
     for (int k = 0; k < 3 && c[k]; ++k) {
@@ -293,10 +314,9 @@ static int fused_tx(const lbm_params* p) {
     return best;
 }
 // Bytes of one h buffer and of one g group of the fused layout.
-static int64_t h_buffer_bytes(const lbm_params* p) {
+static int64_t h_buffer_bytes(const lbm_params* p, int tx) {
     int sh, sg, sphi;
     storage_sizes(p->storage, &sh, &sg, &sphi);
-    const int tx = fused_tx(p);
     return (int64_t)((p->nx + tx - 1) / tx * tx) * p->ny * p->nz * QH * sh;
 }
 static int64_t g_group_bytes(const lbm_params* p) {
@@ -321,15 +341,15 @@ static int64_t g_group_bytes(const lbm_params* p) {
 //   FP64    n = 48: 52 / 36    96: 149 / 161   128: 311 / 328   160: 635 / 616   192: 964 / 1022  256: 2176 / 2333
 //   FP16 g  n = 96: 79 / 51   112: 119 / 111   128: 130 / 144   160: 260 / 260   192: 423 / 431   256: 801 / 936
 constexpr int64_t HYST_FP32_BYTES = (int64_t)3 * 1000 * 1000 * 1000;
-static bool fits_fused(const lbm_params* p) {
+static bool fits_fused(const lbm_params* p, bool beyond) {
     if (phase_q(p) != QH || p->subvoxel) return false;
-    if (p->hysteresis && fused_bytes(p) > CACHED_BYTES) {
+    if (p->hysteresis && beyond) {
         const bool fp32 = p->storage == ST_FP32 || p->storage == ST_FP32_SHIFT;
         if (!fp32 || fused_bytes(p) > HYST_FP32_BYTES) return false;
     }
     if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
     const int64_t lim = (int64_t)1 << 32;
-    return h_buffer_bytes(p) < lim && g_group_bytes(p) < lim;
+    return h_buffer_bytes(p, fused_tx(p, beyond)) < lim && g_group_bytes(p) < lim;
 }
 static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
                            LatticeLayout* L) {
@@ -345,7 +365,7 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
         L->off_pop0 = o; o = align256(o + L->pop_bytes);
         L->off_pop1 = L->off_pop0;
         if (pl.G == 2) { L->off_pop1 = o; o = align256(o + L->pop_bytes); }
-        L->h_bytes = (size_t)h_buffer_bytes(p);
+        L->h_bytes = (size_t)h_buffer_bytes(p, L->tx);
         L->off_h0 = o; o = align256(o + L->h_bytes);
         L->off_h1 = o; o = align256(o + L->h_bytes);
         L->off_flag = o; o = align256(o + (size_t)N);
@@ -440,7 +460,17 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
             }
     L->n_fluid = nf; L->n_ghost = ng; L->n_solid = ns;
     if (nf == 0) { set_error("the lattice has no fluid node"); return LBM_E_INVAL; }
-    bool one_kernel = fused && fits_fused(p);
+    // blocks of 32 nodes of a row that are not all solid
+    int64_t used = 0;
+    const int bx = (nx + 31) / 32;
+    for (int64_t r = 0; r < (int64_t)ny * nz; ++r)
+        for (int x0 = 0; x0 < nx; x0 += 32) {
+            const uint8_t* f = &L->flag[r * nx + x0];
+            for (int x = 0; x < std::min(32, nx - x0); ++x)
+                if (flag_kind(f[x]) != KIND_SOLID) { ++used; break; }
+        }
+    const bool beyond = beyond_cache(p, used, (int64_t)bx * ny * nz);
+    bool one_kernel = fused && fits_fused(p, beyond);
     L->ghosts.clear();
     // ghost owners
     for (int z = 0; z < nz; ++z)
@@ -468,7 +498,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 }
             }
     L->fused = one_kernel;
-    L->back = L->fused && fused_bytes(p) > CACHED_BYTES;
+    L->back = L->fused && beyond;
     // solid links of fluid nodes
     for (int z = 0; z < nz; ++z) {
         const int64_t Z[3] = {(int64_t)((z + nz - 1) % nz) * nx * ny, (int64_t)z * nx * ny,
@@ -560,7 +590,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 }
     }
     // tile table: keep tiles holding at least one non-solid node
-    const int tx = L->fused ? fused_tx(p) : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
+    const int tx = L->fused ? fused_tx(p, beyond) : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
     auto list_tiles = [&](int tz, std::vector<Tile>* tiles) {
         tiles->clear();
@@ -613,7 +643,7 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
         d->nxh = (p->nx + L.tx - 1) / L.tx * L.tx;
         d->hb[0] = base + L.off_h0;
         d->hb[1] = base + L.off_h1;
-        d->hbytes = h_buffer_bytes(p);
+        d->hbytes = (int64_t)L.h_bytes;
         d->back = L.back ? 1 : 0;
         d->march = L.rtiles.empty() ? 0 : 1;
     } else {

@@ -64,3 +64,39 @@ def test_idle_rows_count(shape, tiles, storage, monkeypatch):
         for x, y in zip(a.fields() + a.pops(), b.fields() + b.pops()):
             assert np.isfinite(y).all()
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("storage,shape,beyond", [
+    ("fp32_shift", (120, 120, 120), False),    # 228 MB of populations in 243 MB of lines
+    ("fp32_shift", (128, 128, 128), True),     # 277 MB
+    ("fp32_shift", (17, 256, 256), True),      # 147 MB in 277 MB
+    ("fp16_shift_g", (128, 128, 128), False),  # 197 MB
+    ("fp16_shift_g", (33, 200, 300), True),    # 186 MB in 307 MB
+])
+def test_lines_beyond_the_cache(storage, shape, beyond, monkeypatch):
+    """Lattices whose cache lines, not only whose populations, exceed the Infinity Cache
+    take its tile order and read pass (whose second tile list shows in the footprint
+    of a lattice without walls) and step like the separate passes."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    z, y, x = np.ogrid[:shape[2], :shape[1], :shape[0]]
+    r = np.sqrt((x - 0.5 * shape[0]) ** 2 + (y - 60.3) ** 2 + (z - 58.1) ** 2)
+    wl = inputs.Workload("droplet", *shape, inputs.Physics(nu_g=0.1), inputs.tanh_profile(r - 7.0, 4.0))
+    a = lbm.Lattice(wl, storage=storage)
+    b = separate(monkeypatch, wl, storage)
+    sh, sg = 4, 2 if storage == "fp16_shift_g" else 4
+    info = a.info()
+    row = [w for w in (64, 32, 16) if -(-shape[0] // w) * -(-shape[1] // (256 // w)) * shape[2] == info["n_tiles"]][0]
+    up = lambda v: -(-v // 256) * 256
+    n, nt = wl.n_nodes, info["n_tiles"]
+    plain = 2 * up(-(-shape[0] // row) * row * shape[1] * shape[2] * 7 * sh)
+    plain += up(-(-shape[0] // 64) * 64 * shape[1] * shape[2] * 19 * sg) + up(n) + up(4 * n) + up(32 * nt) + up(80 * nt)
+    second = up(32 * (nt // shape[2]) * -(-shape[2] // 8))
+    extra = info["footprint"] - plain
+    assert (extra >= second) == beyond, (extra, second)
+    for k in (1, 2, 8):
+        a.step(k)
+        b.step(k)
+        for x, y in zip(a.fields(), b.fields()):
+            assert np.isfinite(y).all()
+            assert np.array_equal(x, y)
