@@ -61,3 +61,19 @@ def test_chunked_read_back_from_threads():
     for k in (0, 1):
         for x, y in zip(out[k], lats[k].fields()):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("pinned", ["phi", "u", "phi u"])
+def test_pinned_destination(pinned):
+    """Destinations in pinned memory take plain copies, beside pageable ones in chunks."""
+    require_gpu()
+    import torch
+    from paper_2512_01032_amd import inputs, lbm
+    lat = lbm.Lattice(inputs.random_small(128, 96, 87, seed=44, u_amp=0.002), storage="fp32_shift")
+    lat.step(2)
+    want = lat.read(PHI | 4, noalloc=True)
+    out = {k: torch.full(want[k].shape, 7.0, dtype=torch.float64, pin_memory=k in pinned) for k in want}
+    lbm.check(lbm.lbm_read_fields(lat.h, PHI | 4, out["phi"].data_ptr(), None, out["u"].data_ptr(), None))
+    for k in want:
+        assert out[k].is_pinned() == (k in pinned)
+        assert np.array_equal(out[k].numpy(), want[k]), k
