@@ -210,11 +210,12 @@ int lbm_create(const lbm_params *p, const lbm_geometry *geo, const lbm_init *ini
  * Eqs. 1-16), the pressure-face ghosts (Sec. III.A) and the step counter; for
  * lattices in the fused layout (D3Q7 phase lattice, whole-voxel walls) all of
  * them are one kernel.  The steps are replayed
- * from HIP graphs captured when first needed (one step per AA parity and
- * diagnostic kind, unless a step is one kernel, and 16-step runs without a
- * diagnostic step); while timing is on (lbm_set_timing) every kernel is
- * launched on its own between events instead.  All of these give bitwise the
- * same state.  Returns LBM_E_UNSTABLE if a diagnostic taken before this call
+ * from HIP graphs captured at the first call (one step per AA parity and
+ * diagnostic kind, and 16-step runs without a diagnostic step); steps that are
+ * one kernel are launched as they are in calls of fewer than 64 steps, and the
+ * first longer call captures their 16-step runs.  While timing is on
+ * (lbm_set_timing) every kernel is launched on its own between events instead.
+ * All of these give bitwise the same state.  Returns LBM_E_UNSTABLE if a diagnostic taken before this call
  * flagged NaN or |u| > u_max (sticky). */
 int lbm_step(lbm_handle *h, int64_t nsteps);
 

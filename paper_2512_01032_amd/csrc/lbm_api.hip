@@ -212,11 +212,21 @@ static int capture_steps(lbm_handle* h, int par, int diag, int64_t n, hipGraphEx
     return LBM_OK;
 }
 
-// Capture the graph *g of n steps of this kind unless it is there already.
-static int ensure_graph(lbm_handle* h, int par, int diag, int64_t n, hipGraphExec_t* g) {
-    if (*g) return LBM_OK;
+// Capture the handle's graphs unless they are there already.
+static int ensure_graphs(lbm_handle* h) {
+    if (h->graphs_ready) return LBM_OK;
     if (!h->cap_stream) HIPRET(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
-    return capture_steps(h, par, diag, n, g);
+    for (int par = 0; par < 2; ++par) {
+        for (int diag = 0; diag < 2 && !h->L.fused; ++diag) {
+            if (diag && h->p.diag_every <= 0) continue;
+            int rc = capture_steps(h, par, diag, 1, &h->one[par][diag]);
+            if (rc != LBM_OK) return rc;
+        }
+        int rc = capture_steps(h, par, 0, GRAPH_CHUNK, &h->chunk[par]);
+        if (rc != LBM_OK) return rc;
+    }
+    h->graphs_ready = true;
+    return LBM_OK;
 }
 
 extern "C" int lbm_step(lbm_handle* h, int64_t nsteps) {
@@ -234,23 +244,26 @@ extern "C" int lbm_step(lbm_handle* h, int64_t nsteps) {
         rc = enqueue_steps(h, h->step, nsteps, h->stream, true);
         if (rc != LBM_OK) return rc;
     } else {
+        // a step that is one kernel is launched as it is, but for long calls
+        const bool graphs = !h->L.fused || nsteps >= GRAPH_MIN_STEPS;
+        if (graphs) {
+            rc = ensure_graphs(h);
+            if (rc != LBM_OK) return rc;
+        }
         int64_t k = 0;
         while (k < nsteps) {
             const int64_t t = h->step + k;
             const int par = (int)(t & 1), diag = diag_step(h, t) ? 1 : 0;
-            bool chunk = nsteps - k >= GRAPH_CHUNK;
+            bool chunk = graphs && h->chunk[par] && nsteps - k >= GRAPH_CHUNK;
             if (chunk && de > 0) chunk = ((t + de - 1) / de) * de >= t + GRAPH_CHUNK;
             const int64_t n = chunk ? GRAPH_CHUNK : 1;
             if (!chunk && h->L.fused) {
-                // a single step is one kernel: launched as it is
                 rc = enqueue_steps(h, t, n, h->stream, false);
                 if (rc != LBM_OK) return rc;
             } else {
-                hipGraphExec_t* g = chunk ? &h->chunk[par] : &h->one[par][diag];
-                rc = ensure_graph(h, par, diag, n, g);
-                if (rc != LBM_OK) return rc;
-                if (!*g) { set_error("no step graph for step %lld", (long long)t); return LBM_E_STATE; }
-                HIPRET(hipGraphLaunch(*g, h->stream));
+                hipGraphExec_t g = chunk ? h->chunk[par] : h->one[par][diag];
+                if (!g) { set_error("no step graph for step %lld", (long long)t); return LBM_E_STATE; }
+                HIPRET(hipGraphLaunch(g, h->stream));
             }
             k += n;
         }

@@ -100,3 +100,24 @@ def test_lines_beyond_the_cache(storage, shape, beyond, monkeypatch):
         for x, y in zip(a.fields(), b.fields()):
             assert np.isfinite(y).all()
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("diag_every", [0, 20])
+@pytest.mark.parametrize("first", [0, 3])
+def test_long_calls_replay_graphs(first, diag_every):
+    """Calls of 64 steps and more replay 16-step graphs, from either parity and between
+    diagnostic steps, shorter ones launch every step: the same state."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    wl = inputs.static_droplet(n=24, R=7.0)
+    a = lbm.Lattice(wl, storage="fp32_shift", diag_every=diag_every)
+    b = lbm.Lattice(wl, storage="fp32_shift", diag_every=diag_every)
+    a.step(first)
+    a.step(83)
+    a.step(64)
+    for n in (first, 63, 20, 63, 1):
+        b.step(n)
+    assert a.t == b.t
+    for x, y in zip(a.pops(), b.pops()):
+        assert np.isfinite(y).all()
+        assert np.array_equal(x, y)
