@@ -297,12 +297,13 @@ constexpr int READ_TZ = 8;
 // beyond the cache fewer tiles of 32 than of 64 have any (FP32 ducts n = 128: 162 at 64,
 // 153 at 32; 192: 509, 502; channel 1024 x 64 x 64: 195, 218, against 228 in the
 // separate layout).
-static int fused_tx(const lbm_params* p, bool beyond) {
+static int fused_tx(const lbm_params* p, bool beyond, int most) {
     static const int fp64[3] = {32, 16, 64}, fp64_wide[3] = {32, 64, 0}, cached[3] = {64, 32, 16}, wide[3] = {64, 32, 0}, hyst[3] = {32, 64, 0};
     const int* c = p->storage == ST_FP64 ? (beyond && p->nx > 16 ? fp64_wide : fp64) : (!beyond ? cached : (p->hysteresis ? hyst : wide));
     int best = 0;
     int64_t lanes_best = 0, row_best = 0;
     for (int k = 0; k < 3 && c[k]; ++k) {
+        if (c[k] > most) continue;
         const int tx = c[k], ty = NTHREADS / tx;
         const int64_t row = (p->nx + tx - 1) / tx * tx, lanes = row * ((p->ny + ty - 1) / ty * ty);
         if (!best || lanes < lanes_best || (lanes == lanes_best && row < row_best)) {
@@ -311,7 +312,7 @@ static int fused_tx(const lbm_params* p, bool beyond) {
             row_best = row;
         }
     }
-    return best;
+    return best ? best : most;
 }
 // Bytes of one h buffer and of one g group of the fused layout.
 static int64_t h_buffer_bytes(const lbm_params* p, int tx) {
@@ -341,7 +342,7 @@ static int64_t g_group_bytes(const lbm_params* p) {
 //   FP64    n = 48: 52 / 36    96: 149 / 161   128: 311 / 328   160: 635 / 616   192: 964 / 1022  256: 2176 / 2333
 //   FP16 g  n = 96: 79 / 51   112: 119 / 111   128: 130 / 144   160: 260 / 260   192: 423 / 431   256: 801 / 936
 constexpr int64_t HYST_FP32_BYTES = (int64_t)3 * 1000 * 1000 * 1000;
-static bool fits_fused(const lbm_params* p, bool beyond) {
+static bool fits_fused(const lbm_params* p, bool beyond, int tx) {
     if (phase_q(p) != QH || p->subvoxel) return false;
     if (p->hysteresis && beyond) {
         const bool fp32 = p->storage == ST_FP32 || p->storage == ST_FP32_SHIFT;
@@ -349,7 +350,7 @@ static bool fits_fused(const lbm_params* p, bool beyond) {
     }
     if (tile_z_env() > 0) return false;   // a tile depth asked for: the separate passes have one
     const int64_t lim = (int64_t)1 << 32;
-    return h_buffer_bytes(p, fused_tx(p, beyond)) < lim && g_group_bytes(p) < lim;
+    return h_buffer_bytes(p, tx) < lim && g_group_bytes(p) < lim;
 }
 static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
                            LatticeLayout* L) {
@@ -420,7 +421,8 @@ size_t footprint_bytes(const lbm_params* p) {
     return L.total;
 }
 
-int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fused, LatticeLayout* L) {
+// widest: of the fused layout's tiles
+static int build_layout_of(const lbm_params* p, const lbm_geometry* geo, int lat, bool fused, int widest, LatticeLayout* L) {
     int rc = validate_params(p, geo);
     if (rc != LBM_OK) return rc;
     const int nx = p->nx, ny = p->ny, nz = p->nz;
@@ -470,7 +472,8 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 if (flag_kind(f[x]) != KIND_SOLID) { ++used; break; }
         }
     const bool beyond = beyond_cache(p, used, (int64_t)bx * ny * nz);
-    bool one_kernel = fused && fits_fused(p, beyond);
+    const int ftx = fused_tx(p, beyond, widest);
+    bool one_kernel = fused && fits_fused(p, beyond, ftx);
     L->ghosts.clear();
     // ghost owners
     for (int z = 0; z < nz; ++z)
@@ -590,7 +593,7 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
                 }
     }
     // tile table: keep tiles holding at least one non-solid node
-    const int tx = L->fused ? fused_tx(p, beyond) : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
+    const int tx = L->fused ? ftx : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
     auto list_tiles = [&](int tz, std::vector<Tile>* tiles) {
         tiles->clear();
@@ -622,6 +625,18 @@ int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fus
         for (size_t k = 0; k < v->size(); ++k) (*v)[k].tile_in_lat = (int)k;
     layout_offsets(p, (int64_t)L->tiles.size(), (int64_t)L->ghosts.size(), L);
     return LBM_OK;
+}
+
+int build_layout(const lbm_params* p, const lbm_geometry* geo, int lat, bool fused, LatticeLayout* L) {
+    int rc = build_layout_of(p, geo, lat, fused, 64, L);
+    // lbm_footprint, sized for the separate passes, bounds either layout.  Rows that end
+    // a little past a tile, above all between walls, could go beyond it: they take
+    // narrower tiles, then the separate passes
+    while (rc == LBM_OK && L->fused && L->total > footprint_bytes(p)) {
+        const int tx = L->tx;
+        rc = build_layout_of(p, geo, lat, tx > 16, std::max(tx / 2, 16), L);
+    }
+    return rc;
 }
 
 void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout& L, char* base,

@@ -72,7 +72,7 @@ __host__ __device__ constexpr PopLayout pop_layout(int qp, int sh, int sg) {
     if (tot <= 104) return PopLayout{1, qp + 19, tot};
     int k = 1;
     while (2 * pop_prefix(k, qp, sh, sg) < tot) ++k;
-    if (qp == 0) k += 1 - k % 2;   // g alone: no pair (i, opp(i)) across the cut
+    if (qp == 0) k -= 1 - k % 2;   // g alone: no pair (i, opp(i)) across the cut
     const int a = pop_prefix(k, qp, sh, sg);
     return PopLayout{2, k, a > tot - a ? a : tot - a};
 }

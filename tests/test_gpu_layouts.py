@@ -121,3 +121,33 @@ def test_long_calls_replay_graphs(first, diag_every):
     for x, y in zip(a.pops(), b.pops()):
         assert np.isfinite(y).all()
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32_shift", "fp16_shift_g"])
+@pytest.mark.parametrize("nx", [1, 16, 17, 33, 48, 49, 52, 56, 65, 97, 104, 113, 129])
+def test_footprint_is_a_bound(nx, storage):
+    """lbm_footprint bounds what a lattice takes in the layout it is given: rows a little
+    past a tile or a block, without walls and with a wall link at almost every node."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    for wl in (inputs.random_small(nx, 9, 8, seed=3), porous(nx, 40, 38, 0.3), porous(nx, 40, 38, 0.3, hysteresis=1)):
+        lat = lbm.Lattice(wl, storage=storage)
+        assert lat.info()["footprint"] <= lbm.footprint(wl, storage), wl.name
+
+
+@pytest.mark.parametrize("storage,ny,nz", [("fp32_shift", 200, 300), ("fp16_shift_g", 220, 330)])
+def test_footprint_bounds_narrow_porous_lattices(storage, ny, nz, monkeypatch):
+    """Beyond the cache, rows of 33 in tiles of 64 with a wall link at almost every node
+    would exceed the bound: they take narrower tiles, and step like the separate passes."""
+    require_gpu()
+    from paper_2512_01032_amd import lbm
+    wl = porous(33, ny, nz, 0.2)
+    a = lbm.Lattice(wl, storage=storage)
+    b = separate(monkeypatch, wl, storage)
+    assert a.info()["footprint"] <= lbm.footprint(wl, storage)
+    for n in (1, 2):
+        a.step(n)
+        b.step(n)
+        for x, y in zip(a.fields(), b.fields()):
+            assert np.isfinite(y).all()
+            assert np.array_equal(x, y)
