@@ -410,10 +410,11 @@ int rebuild_tables(lbm_server* s) {
 
 // The launches of one interval (every step starts at the parity of its index).
 // A group in the fused layout needs nothing of the others, so it takes its steps
-// of the interval one after another: its populations stay in the Infinity Cache
-// where those of all groups would not (twelve droplets and channels of 32 to 96
-// nodes a side, 420 MB in three groups: 91.2 -> 79.4 ms; cut further, into
-// batches of at most 96, 160 or 224 MB: 82.5, 82.2, 81.1).
+// of the interval one after another: the populations of a group that fits the
+// Infinity Cache stay there, where those of all groups would not (twelve
+// droplets and channels of 32 to 96 nodes a side, 420 MB in three groups: 91.2
+// -> 79.4 ms; groups cut further, into batches of at most 96, 160 or 224 MB:
+// 82.5, 82.2, 81.1).
 hipError_t enqueue_steps(lbm_server* s, hipStream_t st) {
     const int storage = s->cfg.storage;
     const ReadOut ro = {nullptr, nullptr, nullptr, nullptr};
@@ -647,10 +648,11 @@ extern "C" int lbm_submit(lbm_server* s, const lbm_request* req, uint64_t* ticke
     job->geo.solid = job->solid.empty() ? nullptr : job->solid.data();
     job->geo.sdf = job->sdf.empty() ? nullptr : job->sdf.data();
     // node classification, tile table and arena layout on the caller's
-    // thread: the worker only uploads
+    // thread: the worker only uploads.  The layout is the one that lbm_create
+    // takes, never a smaller one for want of arena: the diagnostic sums of the
+    // two differ in their order, and a result must not depend on what else is
+    // resident (any layout stays within lbm_footprint, checked above).
     rc = build_layout(&job->p, &job->geo, 0, true, &job->L);
-    if (rc == LBM_OK && job->L.fused && job->L.total > s->arena_bytes)
-        rc = build_layout(&job->p, &job->geo, 0, false, &job->L);   // the smaller layout
     if (rc != LBM_OK) return rc;
     job->bytes = job->L.total;
     job->nsteps = req->nsteps;
