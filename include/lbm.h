@@ -263,9 +263,10 @@ int lbm_reduce(lbm_handle *h, lbm_diag *d);
 /* Optional per-kernel timing with HIP events on the handle's stream: while on,
  * lbm_step launches each kernel on its own and records events around them;
  * lbm_get_timing returns the accumulated milliseconds of the phi pass with
- * the wall pass (none in the fused layout), and of the sweep kernel alone (the
- * ghost and step-counter kernels that follow it are not bracketed), and the
- * number of steps timed, and resets them. */
+ * the wall pass (0 in the fused layout), and of the sweep kernel (with the
+ * reduction of its sums on diagnostic steps; the ghost and step-counter
+ * kernels that follow it are not bracketed), and the number of steps timed,
+ * and resets them. */
 int lbm_set_timing(lbm_handle *h, int32_t on);
 int lbm_get_timing(lbm_handle *h, double *phi_ms, double *sweep_ms, int64_t *steps);
 

@@ -151,3 +151,17 @@ def test_footprint_bounds_narrow_porous_lattices(storage, ny, nz, monkeypatch):
         for x, y in zip(a.fields(), b.fields()):
             assert np.isfinite(y).all()
             assert np.array_equal(x, y)
+
+
+def test_timing_of_the_one_kernel_step(monkeypatch):
+    """A lattice in the fused layout has no phi pass to time."""
+    require_gpu()
+    from paper_2512_01032_amd import inputs, lbm
+    wl = inputs.static_droplet(n=24, R=7.0)
+    a, b = lbm.Lattice(wl, storage="fp32_shift"), separate(monkeypatch, wl, "fp32_shift")
+    for lat, phi_pass in ((a, False), (b, True)):
+        lat.set_timing()
+        lat.step(6)
+        phi_ms, sweep_ms, steps = lat.get_timing()
+        assert steps == 6 and sweep_ms > 0.0
+        assert (phi_ms > 0.0) == phi_pass
