@@ -20,18 +20,18 @@
 //
 // What bounds it.  While the populations stay in the 256 MB Infinity Cache a step
 // was bound by its three to five dependent launches (4 to 9 us each) and by the
-// second pass over h: FP32 capillary tube 128^3 76.0 -> 52.0 us a step, channel
-// 1024 x 48 x 32 68.1 -> 43.4, FP64 droplet 32^3 16.3 -> 8.1, 2-D channel
-// 25.0 -> 10.7, FP16 g tube 96^3 with hysteresis 48.7 -> 29.6.  Beyond it HBM bounds
-// the step (4.5 TB/s, duct 256 x 256 x 512, 1083 -> 1027 with plane_order).  Vector
+// second pass over h: FP32 cap 128 x 128 x 96 76.0 -> 52.0 us a step, channel
+// 1024 x 32 x 32 68.1 -> 43.4, FP64 droplet 32^3 16.3 -> 8.1, 2-D channel
+// 25.0 -> 10.7, FP16 g cap 119 x 101 x 67 with hysteresis 48.7 -> 29.6.  Beyond it
+// HBM bounds the step (4.5 TB/s, duct 256 x 256 x 512, 1083 -> 1027 with plane_order).  Vector
 // instructions come next (900 to 1050 per wave): the cells' indexes are shifts and
 // masks and the ring rows wave-uniform (with division by the ring length
-// instead 1000 to 1140, tube 55.7 us, FP16 g duct 192 x 192 x 384 483 us against
+// instead 1000 to 1140, the cap 55.7 us, FP16 g duct 192 x 192 x 384 483 us against
 // 414), and h in blocks of a tile width puts a thread's seven accesses at
 // immediate offsets of one address (414 -> 394 us; h as seven separate rows
 // before).  One node per thread: marching two planes per thread needs more than
 // 128 registers, two planes per 512-thread tile lose more in the barrier than the
-// shared halo gives (tube 59.3 against 55.7 us).
+// shared halo gives (the cap 59.3 against 55.7 us).
 #pragma once
 
 #include <type_traits>
@@ -99,8 +99,8 @@ __device__ inline void push_h(const H& a, const HNbr<H>& nb, uint32_t solid, boo
 // ------------------------------------------------- g of the fused layout
 // The blocked form of the separate passes, g alone.  A node's z-plane is uniform
 // over a wave, so an access is a per-lane (x, y) offset plus a scalar holding
-// plane and direction; dz: -1, 0, +1 plane.  A pair (i, opp(i)) never straddles
-// the two groups of the FP64 layout.
+// plane and direction.  A pair (i, opp(i)) never straddles the two groups of the
+// FP64 layout.
 template <typename LAY> struct GNbr {
     uint32_t x[3], y[3], z[3];
     __device__ void init(int xx, int yy, int zz, int nx, int ny, int nz, int nxp) {
@@ -117,7 +117,7 @@ template <typename LAY> struct GNbr {
         z[2] = (uint32_t)(zz == nz - 1 ? 0 : zz + 1) * plane;
     }
     __device__ uint32_t xy(int i, int s) const { return x[s * CX[i] + 1] + y[s * CY[i] + 1]; }
-    // offset from plane z[1] to the plane of x + s c_i, modulo 2^32
+    // offset of the plane of x + s c_i
     __device__ uint32_t zs(int i, int s) const { return z[s * CZ[i] + 1]; }
 };
 // Keeps a wave-uniform branch a branch.

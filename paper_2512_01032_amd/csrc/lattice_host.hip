@@ -172,6 +172,12 @@ int choose_tz(const lbm_params* p, int tx, bool fused) {
     return std::min(tz, p->nz);
 }
 
+// LBM_TILE_ORDER=spatial: every tile list stays x fastest, then y, then z.
+static bool keep_spatial_order() {
+    const char* env = getenv("LBM_TILE_ORDER");
+    return env && strcmp(env, "spatial") == 0;
+}
+
 // Workgroups go to the eight XCDs round-robin (block b to XCD b mod 8), and
 // each XCD has its own L2.  The tile list (x fastest, then y, then z) is cut
 // into eight contiguous segments and interleaved so that XCD k walks segment
@@ -182,8 +188,7 @@ int choose_tz(const lbm_params* p, int tx, bool fused) {
 void xcd_order(std::vector<Tile>& t) {
     constexpr int NX = 8;
     const int64_t n = (int64_t)t.size();
-    const char* env = getenv("LBM_TILE_ORDER");
-    if (n < 2 * NX || (env && strcmp(env, "spatial") == 0)) return;
+    if (n < 2 * NX || keep_spatial_order()) return;
     const int64_t S = (n + NX - 1) / NX, r = n - NX * (S - 1);
     std::vector<Tile> o;
     o.reserve((size_t)n);
@@ -202,6 +207,7 @@ void xcd_order(std::vector<Tile>& t) {
 // XCD meets its own rows again in the next plane.
 void plane_order(std::vector<Tile>& t) {
     constexpr size_t NX = 8;
+    if (keep_spatial_order()) return;
     std::vector<Tile> q[NX], o;
     o.reserve(t.size());
     size_t extra = 0;   // the longer parts go round the XCDs
@@ -287,9 +293,10 @@ constexpr int READ_TZ = 8;
 // form 244 ring cells, 64 x 4 412), wider ones read whole lines of h and g.  FP64
 // rows of 32 are whole lines already.  Beyond the Infinity Cache rows of 16 in 4 or 2
 // bytes cost more than idle lanes, and of FP64 too (cubes of 104 nodes 108 us at 32,
-// 117 at 16, 113.5 in the separate layout; 120: 145, 167; 200: 762, 807).  Within it 32 and 64 are even (FP32 tube of 128^3
-// nodes 51.8 us at 64, 52.2 at 32; channel 1024 x 48 x 32 43.4, 43.8).  us per step of n x n x 2n ducts at
-// widths 64 / 32 / 16:
+// 117 at 16, 113.5 in the separate layout; 120: 145, 167; 200: 762, 807).  Within it
+// 64 stays the first of equals: the largest lattices there are 1 % faster with it (FP32
+// cap 128 x 128 x 96 51.8 us at 64, 52.2 at 32; channel 1024 x 32 x 32 43.4, 43.8), a
+// duct of n = 64 is 10 % slower.  us per step of n x n x 2n ducts at widths 64 / 32 / 16:
 //   FP64    n = 64: 50.4 / 42.5 / 40.8   80: 100 / 76.8 / 65.8   128: 303 / 269 / 284
 //   FP32    n = 64: 22.5 / 20.2 / 20.5   80: 41.1 / 36.4 / 34.8   112: 106 / 108 / 120   176: 379 / 385 / 445   192: 452 / 456 / 517
 //   FP16 g  n = 64: 19.8 / 19.8 / 20.0   80: 38.1 / 34.5 / 32.1   112: 87 / 98 / 90      176: 314 / 330 / 380   192: 365 / 381 / 443
@@ -381,7 +388,6 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
         L->total = o;
         return;
     }
-    o = align256(o + sizeof(unsigned int));
     {
         const PopLayout pl = pop_layout(phase_q(p), sh, sg);
         L->pop_bytes = (size_t)pop_group_bytes(p);
