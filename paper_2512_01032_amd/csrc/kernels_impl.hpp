@@ -747,8 +747,16 @@ wall_kernel(const Desc* __restrict__ descs, const WallRef* __restrict__ walls, i
     T nv[19];
 #pragma unroll
     for (int i = 1; i < 19; ++i) nv[i] = ((solid >> i) & 1u) ? T(0) : phig[nid(i)];
-    const uint32_t* __restrict__ wm = unip(D->wmat);
-    const uint32_t mw[3] = {wm[sl], wm[nwl + sl], wm[2 * nwl + sl]};
+    uint32_t mw[3] = {0u, 0u, 0u};
+    if constexpr (FPAR >= 0) {
+        const uint8_t* __restrict__ flg = unip(D->flag);
+#pragma unroll
+        for (int i = 1; i < 19; ++i)
+            if ((solid >> i) & 1u) mw[(i - 1) / 6] |= (uint32_t)flag_sub(flg[nid(i)]) << (4 * ((i - 1) % 6));
+    } else {
+        const uint32_t* __restrict__ wm = unip(D->wmat);
+        mw[0] = wm[sl]; mw[1] = wm[nwl + sl]; mw[2] = wm[2 * nwl + sl];
+    }
     const T pc = phig[n];
     T nw[3] = {T(0), T(0), T(0)};
     if (uni(D->subvoxel)) {

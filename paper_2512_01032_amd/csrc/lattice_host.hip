@@ -382,7 +382,6 @@ static void layout_offsets(const lbm_params* p, int64_t ntiles, int64_t nghosts,
         L->off_rtiles = o; o = align256(o + L->rtiles.size() * sizeof(Tile));
         L->off_partials = o; o = align256(o + (size_t)ntiles * NPART * sizeof(double));
         L->off_wrefs = o; o = align256(o + L->walls.size() * sizeof(WallRef));
-        L->off_wmat = o; o = align256(o + L->wmat.size() * 4);
         L->off_wslot = o; if (p->hysteresis) o = align256(o + (size_t)N * 4);
         L->off_hyst = o; if (p->hysteresis) o = align256(o + (size_t)(QG - 1) * L->n_wall * sphi);
         L->total = o;
@@ -468,16 +467,19 @@ static int build_layout_of(const lbm_params* p, const lbm_geometry* geo, int lat
             }
     L->n_fluid = nf; L->n_ghost = ng; L->n_solid = ns;
     if (nf == 0) { set_error("the lattice has no fluid node"); return LBM_E_INVAL; }
-    // blocks of 32 nodes of a row that are not all solid
-    int64_t used = 0;
-    const int bx = (nx + 31) / 32;
-    for (int64_t r = 0; r < (int64_t)ny * nz; ++r)
-        for (int x0 = 0; x0 < nx; x0 += 32) {
-            const uint8_t* f = &L->flag[r * nx + x0];
-            for (int x = 0; x < std::min(32, nx - x0); ++x)
-                if (flag_kind(f[x]) != KIND_SOLID) { ++used; break; }
-        }
-    const bool beyond = beyond_cache(p, used, (int64_t)bx * ny * nz);
+    // (the blocks that are not all solid are counted where they decide)
+    const int64_t blocks = (int64_t)((nx + 31) / 32) * ny * nz;
+    bool beyond = beyond_cache(p, blocks, blocks);
+    if (beyond && !beyond_cache(p, 0, blocks)) {
+        int64_t used = 0;
+        for (int64_t r = 0; r < (int64_t)ny * nz; ++r)
+            for (int x0 = 0; x0 < nx; x0 += 32) {
+                const uint8_t* f = &L->flag[r * nx + x0];
+                for (int x = 0; x < std::min(32, nx - x0); ++x)
+                    if (flag_kind(f[x]) != KIND_SOLID) { ++used; break; }
+            }
+        beyond = beyond_cache(p, used, blocks);
+    }
     const int ftx = fused_tx(p, beyond, widest);
     bool one_kernel = fused && fits_fused(p, beyond, ftx);
     L->ghosts.clear();
@@ -542,8 +544,9 @@ static int build_layout_of(const lbm_params* p, const lbm_geometry* geo, int lat
             ++L->n_wall;
         }
     // materials of the solid links, packed per slot
-    L->wmat.assign((size_t)3 * L->walls.size(), 0u);
-    for (const WallRef& w : L->walls) {
+    L->wmat.assign(L->fused ? 0 : (size_t)3 * L->n_wall, 0u);
+    for (size_t k = 0; k < L->walls.size() && !L->fused; ++k) {
+        const WallRef& w = L->walls[k];
         const int64_t n = w.node;
         const int x = (int)(n % nx), y = (int)((n / nx) % ny), z = (int)(n / ((int64_t)nx * ny));
         for (int i = 1; i < 19; ++i) {
@@ -601,31 +604,43 @@ static int build_layout_of(const lbm_params* p, const lbm_geometry* geo, int lat
     // tile table: keep tiles holding at least one non-solid node
     const int tx = L->fused ? ftx : choose_tx(nx), ty = NTHREADS / tx, tz = choose_tz(p, tx, L->fused);
     L->tx = tx; L->ty = ty; L->tz = tz;
-    auto list_tiles = [&](int tz, std::vector<Tile>* tiles) {
-        tiles->clear();
-        for (int z0 = 0; z0 < nz; z0 += tz)
-            for (int y0 = 0; y0 < ny; y0 += ty)
-                for (int x0 = 0; x0 < nx; x0 += tx) {
-                    bool any = false;
-                    const int z1 = std::min(nz, z0 + tz), y1 = std::min(ny, y0 + ty), x1 = std::min(nx, x0 + tx);
-                    for (int z = z0; z < z1 && !any; ++z)
-                        for (int y = y0; y < y1 && !any; ++y)
-                            for (int x = x0; x < x1; ++x)
-                                if (flag_kind(L->flag[x + (int64_t)nx * (y + (int64_t)ny * z)]) != KIND_SOLID) { any = true; break; }
-                    if (!any) continue;
-                    Tile t;
-                    memset(&t, 0, sizeof(t));
-                    t.lat = lat; t.x0 = x0; t.y0 = y0; t.z0 = z0; t.zn = z1 - z0;
-                    tiles->push_back(t);
-                }
-    };
-    list_tiles(tz, &L->tiles);
-    if (L->back) plane_order(L->tiles);
-    else xcd_order(L->tiles);
+    L->tiles.clear();
+    for (int z0 = 0; z0 < nz; z0 += tz)
+        for (int y0 = 0; y0 < ny; y0 += ty)
+            for (int x0 = 0; x0 < nx; x0 += tx) {
+                bool any = false;
+                const int z1 = std::min(nz, z0 + tz), y1 = std::min(ny, y0 + ty), x1 = std::min(nx, x0 + tx);
+                for (int z = z0; z < z1 && !any; ++z)
+                    for (int y = y0; y < y1 && !any; ++y)
+                        for (int x = x0; x < x1; ++x)
+                            if (flag_kind(L->flag[x + (int64_t)nx * (y + (int64_t)ny * z)]) != KIND_SOLID) { any = true; break; }
+                if (!any) continue;
+                Tile t;
+                memset(&t, 0, sizeof(t));
+                t.lat = lat; t.x0 = x0; t.y0 = y0; t.z0 = z0; t.zn = z1 - z0;
+                L->tiles.push_back(t);
+            }
+    // the read pass' tiles: READ_TZ planes of each column that has a tile among them
     L->rtiles.clear();
     if (L->back) {
-        list_tiles(std::min(READ_TZ, nz), &L->rtiles);
+        const int cx = (nx + tx - 1) / tx, cols = cx * ((ny + ty - 1) / ty);
+        std::vector<char> has(cols);
+        for (size_t i = 0, j; i < L->tiles.size(); i = j) {
+            const int z0 = L->tiles[i].z0 / READ_TZ * READ_TZ;
+            std::fill(has.begin(), has.end(), 0);
+            for (j = i; j < L->tiles.size() && L->tiles[j].z0 < z0 + READ_TZ; ++j)
+                has[L->tiles[j].x0 / tx + cx * (L->tiles[j].y0 / ty)] = 1;
+            for (int c = 0; c < cols; ++c) {
+                if (!has[c]) continue;
+                Tile t = L->tiles[i];
+                t.x0 = c % cx * tx; t.y0 = c / cx * ty; t.z0 = z0; t.zn = std::min(READ_TZ, nz - z0);
+                L->rtiles.push_back(t);
+            }
+        }
+        plane_order(L->tiles);
         xcd_order(L->rtiles);
+    } else {
+        xcd_order(L->tiles);
     }
     for (std::vector<Tile>* v : {&L->tiles, &L->rtiles})
         for (size_t k = 0; k < v->size(); ++k) (*v)[k].tile_in_lat = (int)k;
@@ -671,8 +686,8 @@ void fill_desc(const lbm_params* p, const lbm_geometry* geo, const LatticeLayout
         d->phi = base + L.off_phi;
         d->gbuf = base + L.off_gbuf;
         d->wgl = base + L.off_wgl;
+        d->wmat = (const uint32_t*)(base + L.off_wmat);
     }
-    d->wmat = (const uint32_t*)(base + L.off_wmat);
     d->q_phase = phase_q(p);
     d->hysteresis = p->hysteresis;
     d->hyst_reset = 0;
@@ -791,7 +806,8 @@ int upload_and_init(const lbm_params* p, const lbm_geometry* geo, const lbm_init
     if (!L.walls.empty()) {
         HIPCHK(hipMemcpyAsync(base + L.off_wrefs, L.walls.data(), L.walls.size() * sizeof(WallRef),
                               hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(base + L.off_wmat, L.wmat.data(), L.wmat.size() * 4, hipMemcpyHostToDevice, s));
+        if (!L.wmat.empty())
+            HIPCHK(hipMemcpyAsync(base + L.off_wmat, L.wmat.data(), L.wmat.size() * 4, hipMemcpyHostToDevice, s));
     }
     if (p->subvoxel && L.n_wall) {
         // wall table in the compute type (a synchronous copy: the host

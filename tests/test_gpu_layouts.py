@@ -328,7 +328,7 @@ def test_allocation_failure_takes_separate_passes(monkeypatch):
                 held.append(torch.empty(block, dtype=torch.uint8, device="cuda"))
         except torch.OutOfMemoryError:
             pass
-        back = -(-(fused + sep) // 2 // block)
+        back = -(-sep // block)
         assert sep < back * block < fused and len(held) > back
         del held[-back:]
         torch.cuda.empty_cache()
