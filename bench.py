@@ -716,8 +716,9 @@ def main():
             "sweep_frac_hbm": achieved / HBM_PEAK_GBS,
             "step_GBs_alg": b_alg * nf * args.steps / el / 1e9,
         }
-        # the same number of steps again through lbm_step's captured graphs
-        # (no events): the rate a caller of the library sees
+        # the same number of steps again as lbm_step runs them without events (from
+        # captured graphs, or plain launches in short calls where a step is one
+        # kernel): the rate a caller of the library sees
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         lat.step(args.steps)
